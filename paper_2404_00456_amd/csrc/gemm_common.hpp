@@ -4,6 +4,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "gemm_plan.hpp"
 
 namespace quarot {
 namespace gemm {
@@ -113,4 +114,9 @@ constexpr int waitcnt_imm(int vm, int lgkm)
 }
 
 }  // namespace gemm
+
+// The streaming kernels of gemm_stream.hip (few X rows); codes as launch_gemm.
+hipError_t launch_gemm_stream(const GemmArgs &a, const gemm::StreamPlan &p, int bits,
+                              hipStream_t s);
+
 }  // namespace quarot

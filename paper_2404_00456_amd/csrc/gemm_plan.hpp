@@ -57,5 +57,55 @@ inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int cus, in
             (int)grid};
 }
 
+// The streaming kernels' plan (gemm_stream.hip): tile 16 mt x 16 nt, blocks;
+// mt = 0: the problem takes the tiled plan above.
+struct StreamPlan {
+    int mt, nt, grid;
+};
+
+// A block of the streaming kernels reads its nt W slices and its X rows once
+// per k-step, at a rate that hardly depends on the tile, so the time goes
+// with rounds of blocks over the CUs times (16 nt + rows).  That product
+// picked the fastest of nt = 1, 2, 4 in 117 of 120 measured shapes (e3m2,
+// int4 and int8 codes, M = 1 .. 256, N = 1024 .. 28672, K = 4096 .. 28672),
+// within 9% in the others: wide tiles where N gives every CU a block all the same
+// (N = 28672, M = 61: nt = 1, 2, 4 take 68, 52, 40 us), narrow ones where it
+// does not (N = 4096, K = 4096: 5.3, 6.2, 7.9 us).
+//
+// Against the tiled kernels the estimate is 2 us and STREAM ns per row of
+// the sum above and k-step, against 8 us and TILED ns per round of tiles
+// and k-step (twice that for 256-row tiles with more than 128 rows in use).
+// Both were fitted to the same shapes: 256 x 28672, K = 8192 takes 104 us
+// streamed and 60 us tiled, 256 x 8192, K = 28672 88 and 168 us.
+inline StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int bits, int cus, int stages)
+{
+    if (bits == 4 && K % 128 != 0)
+        return {0, 0, 0};
+    const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+    const int64_t rows = M < 16 * mt ? M : 16 * mt;
+    const int64_t TM = (M + 16 * mt - 1) / (16 * mt);
+    int best = 0;
+    int64_t units = 0, grid = 0;
+    for (int nt = 1; nt <= 4; nt *= 2) {
+        const int64_t blocks = TM * ((N + 16 * nt - 1) / (16 * nt));
+        const int64_t u = (blocks + cus - 1) / cus * (16 * nt + rows);
+        if (!best || u < units) {
+            best = nt;
+            units = u;
+            grid = blocks;
+        }
+    }
+    const GemmPlan g = plan_gemm(M, N, K, bits, cus, stages);
+    const int64_t ksteps = bits == 8 ? K / 64 : K / 128;
+    const int64_t half = g.kernel == GemmKernel::Tile256 ? 256 : 128;
+    const int64_t tiles = (M + half - 1) / half * ((N + 255) / 256);
+    const int64_t rounds = (tiles + g.grid - 1) / g.grid;
+    const int64_t full = half == 256 && M > 128 ? 2 : 1;
+    const int64_t stream = bits == 6 ? 180 : 210, tiled = bits == 4 ? 1200 : 600;  // 1/100, 1 ns
+    if (2000 + units * ksteps * stream / 100 >= 8000 + rounds * full * ksteps * tiled)
+        return {0, 0, 0};
+    return {mt, best, (int)grid};
+}
+
 }  // namespace gemm
 }  // namespace quarot

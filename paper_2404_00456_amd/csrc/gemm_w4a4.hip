@@ -1292,6 +1292,9 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s, int bits)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         cus = 256;
+    const StreamPlan sp = plan_stream(a.M, a.N, a.K, bits, cus, S);
+    if (sp.mt)
+        return launch_gemm_stream(a, sp, bits, s);
     const GemmPlan plan = plan_gemm(a.M, a.N, a.K, bits, cus, S);
     const int grid = plan.grid;
     if (plan.kernel == GemmKernel::K64) {
