@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libquarot.so")
 SOURCES = ["capi.cpp", "host_rules.cpp", "rotate_quant.hip", "gemm_w4a4.hip", "gemm_stream.hip",
-           "gemm_grouped.hip", "kv_attention.hip", "scratch.hip"]
+           "gemm_mid.hip", "gemm_grouped.hip", "kv_attention.hip", "scratch.hip"]
 # MFMA-only rate probes and the device's peak clock (include/quarot_probe.h)
 PROBE_LIB = os.path.join(HERE, "libquarot_probe.so")
 PROBE_SOURCES = ["probe.hip"]

@@ -116,7 +116,9 @@ constexpr int waitcnt_imm(int vm, int lgkm)
 }  // namespace gemm
 
 // The streaming kernels of gemm_stream.hip (few X rows); codes as launch_gemm.
-hipError_t launch_gemm_stream(const GemmArgs &a, const gemm::StreamPlan &p, int bits,
+hipError_t launch_gemm_stream(const GemmArgs &a, const gemm::PathPlan &p, int bits,
                               hipStream_t s);
+// The ring kernels of gemm_mid.hip (middling grids).
+hipError_t launch_gemm_mid(const GemmArgs &a, const gemm::PathPlan &p, int bits, hipStream_t s);
 
 }  // namespace quarot

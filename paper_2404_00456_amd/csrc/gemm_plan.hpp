@@ -57,54 +57,96 @@ inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int cus, in
             (int)grid};
 }
 
-// The streaming kernels' plan (gemm_stream.hip): tile 16 mt x 16 nt, blocks;
-// mt = 0: the problem takes the tiled plan above.
-struct StreamPlan {
-    int mt, nt, grid;
+// The path of a product: the tiled plan above, or the kernels for fewer rows
+// or outputs than fill it.
+enum class GemmPath {
+    Tiled,   // plan_gemm
+    Stream,  // gemm_stream.hip, tile 16 a x 16 b
+    Mid,     // gemm_mid.hip, tile 32 a x 64 b
 };
 
-// A block of the streaming kernels reads its nt W slices and its X rows once
-// per k-step, at a rate that hardly depends on the tile, so the time goes
-// with rounds of blocks over the CUs times (16 nt + rows).  That product
-// picked the fastest of nt = 1, 2, 4 in 117 of 120 measured shapes (e3m2,
-// int4 and int8 codes, M = 1 .. 256, N = 1024 .. 28672, K = 4096 .. 28672),
-// within 9% in the others: wide tiles where N gives every CU a block all the same
-// (N = 28672, M = 61: nt = 1, 2, 4 take 68, 52, 40 us), narrow ones where it
-// does not (N = 4096, K = 4096: 5.3, 6.2, 7.9 us).
-//
-// Against the tiled kernels the estimate is 2 us and STREAM ns per row of
-// the sum above and k-step, against 8 us and TILED ns per round of tiles
-// and k-step (twice that for 256-row tiles with more than 128 rows in use).
-// Both were fitted to the same shapes: 256 x 28672, K = 8192 takes 104 us
-// streamed and 60 us tiled, 256 x 8192, K = 28672 88 and 168 us.
-inline StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, int bits, int cus, int stages)
+struct PathPlan {
+    GemmPath path;
+    int a, b, grid;
+};
+
+// Times are estimated in ns and the smallest wins.  The constants were fitted
+// to 327 measured shapes (e3m2, int4 and int8 codes; M = 1 .. 8000, N = 1024
+// .. 28672, K = 4096 .. 28672, 256 CUs): the choice took 0.3% more time than
+// the best kernel of each shape on average, and none of them lost more than 2%
+// against the tiled kernels.  A kernel's time is a start-up plus rounds of
+// its blocks over the CUs times k-steps times what one step of a tile takes:
+//  * Stream: a block's time per k-step goes with its 16 b columns plus its
+//    rows, at a rate set by the CU (LO) or, with every CU busy, by the L2s
+//    (HI).  Of its widths b, rounds * (16 b + rows) picks the fastest (within
+//    9% in 120 shapes): wide where N gives every CU a block all the same
+//    (61 x 28672, K = 8192: 1, 2, 4 take 68, 52, 40 us), narrow where it does not
+//    (61 x 4096, K = 4096: 5.3, 6.2, 7.9 us).
+//  * Mid: STEP, a fifth more for the small tiles when they come in several
+//    rounds (their operand traffic then meets the L2s' limit).
+//  * Tiled: the 128-row tiles take 530 to 1250 ns per k-step, the 256-row
+//    tiles 850 to 1500 (600 when half of them is padding); the split-k kernel
+//    starts up in 11 us and waits for HBM when W exceeds the last-level cache.
+// For instance 333 x 11008, K = 4096 on e3m2: stream 33 us, mid 128 x 192
+// 18.7, tiled 28.4; 2048 x 4096, K = 11008: mid 58.4, tiled 55.5.
+inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, int stages)
 {
     if (bits == 4 && K % 128 != 0)
-        return {0, 0, 0};
+        return {GemmPath::Tiled, 0, 0, 0};
+    auto up = [](int64_t x, int64_t d) { return (x + d - 1) / d; };
+    constexpr int64_t MOST = 0x7FFFFFFF;  // blocks of a grid
+    const int64_t ks = bits == 8 ? K / 64 : K / 128;
+    const int f = bits == 6 ? 0 : bits == 4 ? 1 : 2;
+
+    const GemmPlan g = plan_gemm(M, N, K, bits, cus, stages);
+    const bool big = g.kernel == GemmKernel::Tile256;
+    const int64_t rounds = up(up(M, big ? 256 : 128) * up(N, 256), g.grid);
+    int64_t step;
+    if (big)
+        step = M > 128 ? (bits == 6 ? 980 : bits == 4 ? 1500 : 850)
+                       : (bits == 6 ? 600 : bits == 4 ? 1250 : 610);
+    else
+        step = bits == 6 ? (N * K > 100000000 ? 660 : 530) : bits == 4 ? 1250 : 610;
+    int64_t best = (g.kernel == GemmKernel::Ksplit ? 11000 : 8000) + rounds * ks * step;
+    PathPlan plan = {GemmPath::Tiled, 0, 0, 0};
+
     const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-    const int64_t rows = M < 16 * mt ? M : 16 * mt;
-    const int64_t TM = (M + 16 * mt - 1) / (16 * mt);
-    int best = 0;
-    int64_t units = 0, grid = 0;
-    for (int nt = 1; nt <= 4; nt *= 2) {
-        const int64_t blocks = TM * ((N + 16 * nt - 1) / (16 * nt));
-        const int64_t u = (blocks + cus - 1) / cus * (16 * nt + rows);
-        if (!best || u < units) {
-            best = nt;
+    const int64_t rows = M < 16 * mt ? M : 16 * mt, tm = up(M, 16 * mt);
+    int nt = 0;
+    int64_t units = 0, blocks = 0;
+    for (int b = 1; b <= 4; b *= 2) {
+        const int64_t n = tm * up(N, 16 * b), u = up(n, cus) * (16 * b + rows);
+        if (nt == 0 || u < units) {
+            nt = b;
             units = u;
-            grid = blocks;
+            blocks = n;
         }
     }
-    const GemmPlan g = plan_gemm(M, N, K, bits, cus, stages);
-    const int64_t ksteps = bits == 8 ? K / 64 : K / 128;
-    const int64_t half = g.kernel == GemmKernel::Tile256 ? 256 : 128;
-    const int64_t tiles = (M + half - 1) / half * ((N + 255) / 256);
-    const int64_t rounds = (tiles + g.grid - 1) / g.grid;
-    const int64_t full = half == 256 && M > 128 ? 2 : 1;
-    const int64_t stream = bits == 6 ? 180 : 210, tiled = bits == 4 ? 1200 : 600;  // 1/100, 1 ns
-    if (2000 + units * ksteps * stream / 100 >= 8000 + rounds * full * ksteps * tiled)
-        return {0, 0, 0};
-    return {mt, best, (int)grid};
+    const int64_t lo = bits == 6 ? 145 : 190, hi = bits == 6 ? 175 : 210;  // 1/100 ns
+    const int64_t cu = lo * units, l2 = hi * blocks * (16 * nt + rows) / cus;
+    const int64_t stream = 2000 + ks * (cu > l2 ? cu : l2) / 100;
+    if (stream < best && blocks <= MOST) {
+        best = stream;
+        plan = {GemmPath::Stream, mt, nt, (int)blocks};
+    }
+
+    static constexpr struct {
+        int a, b, step[3], more;  // ns per k-step (e3m2, int4, int8); percent in several rounds
+    } mids[] = {
+        {2, 1, {190, 225, 120}, 120}, {2, 2, {250, 350, 195}, 120}, {4, 2, {365, 540, 270}, 120},
+        {4, 3, {520, 750, 400}, 105}, {4, 4, {690, 920, 560}, 100}, {8, 3, {890, 1250, 740}, 100},
+    };
+    for (const auto &m : mids) {
+        const int64_t n = up(M, 32 * m.a) * up(N, 64 * m.b), r = up(n, cus);
+        // 3% on the safe side
+        const int64_t t = (2500 + r * (ks * m.step[f] * (r > 1 ? m.more : 100) / 100 + 1000)) *
+                          103 / 100;
+        if (t < best && n <= MOST) {
+            best = t;
+            plan = {GemmPath::Mid, m.a, m.b, (int)n};
+        }
+    }
+    return plan;
 }
 
 }  // namespace gemm

@@ -307,9 +307,9 @@ hipError_t go(const GemmArgs &a, int grid, hipStream_t s)
 // the registers of two blocks per CU where the tile is small, of one where
 // it is not.
 template <int BITS>
-hipError_t pick(const GemmArgs &a, const StreamPlan &p, hipStream_t s)
+hipError_t pick(const GemmArgs &a, const PathPlan &p, hipStream_t s)
 {
-    switch (10 * p.mt + p.nt) {
+    switch (10 * p.a + p.b) {
     case 11: return go<BITS, 1, 1, 8, 4>(a, p.grid, s);
     case 12: return go<BITS, 1, 2, 8, 4>(a, p.grid, s);
     case 14: return go<BITS, 1, 4, 8, 2>(a, p.grid, s);
@@ -325,7 +325,7 @@ hipError_t pick(const GemmArgs &a, const StreamPlan &p, hipStream_t s)
 
 }  // namespace
 
-hipError_t launch_gemm_stream(const GemmArgs &a, const StreamPlan &p, int bits, hipStream_t s)
+hipError_t launch_gemm_stream(const GemmArgs &a, const PathPlan &p, int bits, hipStream_t s)
 {
     hipError_t e = bits == 6 ? pick<6>(a, p, s) : bits == 8 ? pick<8>(a, p, s) : pick<4>(a, p, s);
     return e != hipSuccess ? e : hipGetLastError();

@@ -1292,9 +1292,11 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s, int bits)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         cus = 256;
-    const StreamPlan sp = plan_stream(a.M, a.N, a.K, bits, cus, S);
-    if (sp.mt)
-        return launch_gemm_stream(a, sp, bits, s);
+    const PathPlan path = plan_path(a.M, a.N, a.K, bits, cus, S);
+    if (path.path == GemmPath::Stream)
+        return launch_gemm_stream(a, path, bits, s);
+    if (path.path == GemmPath::Mid)
+        return launch_gemm_mid(a, path, bits, s);
     const GemmPlan plan = plan_gemm(a.M, a.N, a.K, bits, cus, S);
     const int grid = plan.grid;
     if (plan.kernel == GemmKernel::K64) {

@@ -1,0 +1,87 @@
+// The choice between the GEMM kernels (csrc/gemm_plan.hpp), built for the
+// host: over a sweep of shapes, code widths and CU counts every plan is a
+// compiled tile whose grid covers the output exactly once, int4 codes with K
+// not a multiple of 128 stay on the tiled path, and shapes the rule was
+// fitted to fall on the side that was measured faster.
+#include <cstdio>
+#include <initializer_list>
+
+#include "gemm_plan.hpp"
+
+using quarot::gemm::GemmPath;
+using quarot::gemm::plan_path;
+
+int main()
+{
+    const long long Ms[] = {1,  15,  16,  17,  32,   33,    64,      65,
+                            90, 128, 333, 517, 1024, 16384, 1 << 20, 1 << 30};
+    const long long Ns[] = {1, 16, 17, 250, 1376, 4096, 8190, 11008, 28672, 1 << 20};
+    const long long Ks[] = {64, 128, 192, 256, 4096, 11008, 28672, 65536};
+    int failures = 0, taken[3] = {0, 0, 0};
+    for (long long M : Ms)
+        for (long long N : Ns)
+            for (long long K : Ks)
+                for (int bits : {4, 6, 8})
+                    for (int cus : {64, 256, 304}) {
+                        if (bits == 6 && K % 128)
+                            continue;
+                        if ((M + 255) / 256 * ((N + 255) / 256) > 0x7FFFFFFF)
+                            continue;  // refused before planning
+                        const auto p = plan_path(M, N, K, bits, cus, 3);
+                        ++taken[(int)p.path];
+                        if (p.path == GemmPath::Tiled)
+                            continue;
+                        const int t = 10 * p.a + p.b;
+                        bool ok;
+                        long long um, un;
+                        if (p.path == GemmPath::Stream) {
+                            ok = t == 11 || t == 12 || t == 14 || t == 21 || t == 22 || t == 24 ||
+                                 t == 41 || t == 42 || t == 44;
+                            um = 16 * p.a;
+                            un = 16 * p.b;
+                        } else {
+                            ok = t == 21 || t == 22 || t == 42 || t == 43 || t == 44 || t == 83;
+                            um = 32 * p.a;
+                            un = 64 * p.b;
+                        }
+                        const long long want = (M + um - 1) / um * ((N + un - 1) / un);
+                        if (!ok || p.grid != want || (bits == 4 && K % 128)) {
+                            std::printf("FAIL M=%lld N=%lld K=%lld bits=%d: path %d %d %d grid %d\n",
+                                        M, N, K, bits, (int)p.path, p.a, p.b, p.grid);
+                            ++failures;
+                        }
+                    }
+    for (int n : taken)
+        if (!n) {
+            std::printf("FAIL a path is never taken\n");
+            ++failures;
+        }
+    const GemmPath T = GemmPath::Tiled, S = GemmPath::Stream, D = GemmPath::Mid;
+    const struct {
+        long long M, N, K;
+        int bits;
+        GemmPath path;
+        int a, b;
+    } fitted[] = {
+        {1, 4096, 4096, 6, S, 1, 1},     {16, 8192, 28672, 6, S, 1, 2},
+        {16, 28672, 8192, 6, S, 1, 4},   {33, 28672, 8192, 4, S, 4, 4},
+        {61, 8192, 28672, 6, S, 4, 2},   {128, 28672, 8192, 6, D, 4, 2},
+        {333, 11008, 4096, 6, D, 4, 3},  {1024, 4096, 4096, 6, D, 4, 2},
+        {2048, 4096, 11008, 6, T, 0, 0}, {16384, 28672, 8192, 6, T, 0, 0},
+        {16384, 8192, 28672, 6, T, 0, 0}, {1777, 4096, 4096, 4, D, 4, 4},
+        {16384, 28672, 8192, 4, T, 0, 0}, {517, 5120, 13824, 8, D, 4, 2},
+        {32, 4096, 11008, 8, S, 2, 1},   {3000, 8192, 8192, 8, T, 0, 0},
+    };
+    for (const auto &c : fitted) {
+        const auto p = plan_path(c.M, c.N, c.K, c.bits, 256, 3);
+        if (p.path != c.path || p.a != c.a || p.b != c.b) {
+            std::printf("FAIL M=%lld N=%lld K=%lld bits=%d: path %d tile %d x %d, want %d %d x %d\n",
+                        c.M, c.N, c.K, c.bits, (int)p.path, p.a, p.b, (int)c.path, c.a, c.b);
+            ++failures;
+        }
+    }
+    if (failures)
+        return 1;
+    std::printf("ok\n");
+    return 0;
+}

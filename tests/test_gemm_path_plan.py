@@ -1,6 +1,6 @@
-"""The streaming GEMMs' choice of tile and grid (csrc/gemm_plan.hpp), built
+"""The choice between the streaming, middling and tiled GEMMs and of their tile and grid (csrc/gemm_plan.hpp), built
 for the host with the address and undefined-behaviour sanitizers
-(tests/native/stream_plan_check.cpp).  Nothing runs on a GPU."""
+(tests/native/gemm_path_check.cpp).  Nothing runs on a GPU."""
 import os
 import shutil
 import subprocess
@@ -9,12 +9,12 @@ import tempfile
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "tests", "native", "stream_plan_check.cpp")
+SRC = os.path.join(ROOT, "tests", "native", "gemm_path_check.cpp")
 CSRC = os.path.join(ROOT, "paper_2404_00456_amd", "csrc")
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-def test_stream_plans():
+def test_gemm_paths():
     with tempfile.TemporaryDirectory() as d:
         exe = os.path.join(d, "check")
         subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=address,undefined",
