@@ -167,4 +167,35 @@ struct HmMfmaB {
     }
 };
 
+// H_m transposed as the fp16 A operand of v_mfma_f32_16x16x32_f16, for the
+// rotation's rows of at least 16 groups: output tile ct (16 columns b'),
+// k-block kb (32 inputs), lane l holds 8 halves, half e =
+// H[kb*32 + (l/16)*8 + e][ct*16 + l%16] (+1 / -1), 0 past the edge.  Stored as
+// dwords, 4 per lane.
+template <int M>
+struct HmF16A {
+    static constexpr int CT = (M + 15) / 16;
+    static constexpr int KB = (M + 31) / 32;
+    uint32_t w[CT][KB][64][4];
+    constexpr HmF16A() : w()
+    {
+        const Gs43Rows g{};
+        for (int ct = 0; ct < CT; ++ct)
+            for (int kb = 0; kb < KB; ++kb)
+                for (int l = 0; l < 64; ++l)
+                    for (int q = 0; q < 4; ++q) {
+                        uint32_t word = 0;
+                        for (int j = 0; j < 2; ++j) {
+                            const int r = kb * 32 + (l / 16) * 8 + 2 * q + j;
+                            const int c = ct * 16 + l % 16;
+                            int v = 0;
+                            if (r < M && c < M)
+                                v = M == 172 ? gs172_sign(g, r, c) : hm_sign(M, r, c);
+                            word |= (v > 0 ? 0x3C00u : v < 0 ? 0xBC00u : 0u) << (16 * j);
+                        }
+                        w[ct][kb][l][q] = word;
+                    }
+    }
+};
+
 }  // namespace quarot

@@ -19,9 +19,11 @@
 //                 lanes, then across the W waves (LDS), then across chunks.
 //   k_rot_smallm  m = 12, 20, 28: each lane owns whole groups of m elements;
 //                 the m-factor is an fp64 sum with shared partial sums.
-//   k_rot_largem  m = 108, 172: the m-factor as exact integer digit
-//                 products on the int8 matrix cores, the rotated row staged
-//                 in LDS.
+//   k_rot_largem_f16  m = 108, 172 and 2^k >= 16: the m-factor as exact
+//                 products of split fp16 inputs on the fp16 matrix cores, the
+//                 rotated row in registers.
+//   k_rot_largem  m = 108, 172 and 2^k < 16: exact integer digit products on
+//                 the int8 matrix cores, the rotated row staged in LDS.
 //   k_quant_plain quantization without rotation, any n multiple of 8.
 //   k_kv_dequant  4-bit KV cache back to fp16, optional inverse rotation.
 // Lane butterflies use the placement and sign bookkeeping of lane_stages().
@@ -38,6 +40,8 @@ typedef int v6i __attribute__((ext_vector_type(6)));
 
 __constant__ HmMfmaB<108> c_hmb108 = HmMfmaB<108>();
 __constant__ HmMfmaB<172> c_hmb172 = HmMfmaB<172>();
+__constant__ HmF16A<108> c_hfa108 = HmF16A<108>();
+__constant__ HmF16A<172> c_hfa172 = HmF16A<172>();
 
 namespace {
 
@@ -275,7 +279,17 @@ __device__ __forceinline__ float silu_f32(float g)
     p = __builtin_fmaf(p, r, 1.0f);
     p = __builtin_fmaf(p, r, 1.0f);
     const float e = __builtin_ldexpf(p, (int)kf);
-    return g / (1.0f + e);
+    // RN(g / d): a Newton step on the reciprocal estimate and Markstein's
+    // correction, without the scaling of the general division (d is in
+    // [1, 2^127); where 1 / d would be subnormal the quotient is far below
+    // fp16 and only its sign counts, which is g's).  For every finite fp16 gate
+    // this is the IEEE quotient's encoding down to 2^-110 and a zero or that
+    // quotient below.
+    const float d = 1.0f + e;
+    float r0 = __builtin_amdgcn_rcpf(d);
+    r0 = __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);
+    const float q0 = g * r0;
+    return __builtin_copysignf(__builtin_fmaf(__builtin_fmaf(-d, q0, g), r0, q0), g);
 }
 
 // The down-projection input h = RN16(RN(silu(g) u)), as binary32.
@@ -1203,6 +1217,361 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem(RotArgs a)
     }
 }
 
+// ---- m = 108, 172 and at least 16 groups: the m-factor on the fp16 cores ----
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <int M>
+__device__ __forceinline__ const uint4 *hm_f16_a();
+template <>
+__device__ __forceinline__ const uint4 *hm_f16_a<108>()
+{
+    return reinterpret_cast<const uint4 *>(&c_hfa108.w[0][0][0][0]);
+}
+template <>
+__device__ __forceinline__ const uint4 *hm_f16_a<172>()
+{
+    return reinterpret_cast<const uint4 *>(&c_hfa172.w[0][0][0][0]);
+}
+
+__device__ __forceinline__ v2h rint2(v2h v)
+{
+    return __builtin_elementwise_rint(v);
+}
+
+// Two fp16 inputs with |t| < 512 as t 2^7 = h + l 2^-10, all fp16 and exact:
+// h = rint(t 2^7), |h| <= 65504, and l = (t 2^7 - h) 2^10, a multiple of 2^-7
+// with |l| <= 512 (t 2^7 is a multiple of 2^-17, and the difference has no
+// more significant bits than t).
+__device__ __forceinline__ void f16_split(v2h t, v2h &h, v2h &l)
+{
+    const v2h s = t * v2h{(_Float16)128.0f, (_Float16)128.0f};
+    h = rint2(s);
+    l = (s - h) * v2h{(_Float16)1024.0f, (_Float16)1024.0f};
+}
+
+template <int M, int RT, int EPI>
+struct LargemLds {
+    static constexpr int PLANE = RT * HmF16A<M>::KB * 1024;
+    static constexpr int N = M * 16 * RT;
+    static constexpr int STAGE = EPI == EPI_F16 ? 2 * N : EPI == EPI_SYM ? N / 2
+                                                      : EPI == EPI_F32  ? 0 : N;
+    static constexpr int BYTES = 2 * PLANE > STAGE ? 2 * PLANE : STAGE;
+};
+
+// Rows of A = 16 RT groups of M elements (element i = g M + b), one row at a
+// time per block of four waves.
+//
+// m-factor: U^T = H_M^T . T^T with T the groups [A, M].  Where every |t| < 512
+// the row is split by f16_split and multiplied by +-1 twice: sum h is an
+// integer of magnitude at most 172 * 65504 < 2^24 and sum l a multiple of 2^-7
+// below 172 * 512, so v_mfma_f32_16x16x32_f16 accumulates both exactly in any
+// order, and fma(sum l, 2^-10, sum h) is 2^7 u with the one rounding the
+// definition asks for.  The factor 2^-7 joins c, exactly.  (A row with larger
+// values takes a third operand and binary64 at the end, see below.)
+//
+// The four waves split the row into operands, 32 inputs of 16 groups at a
+// time, through LDS; each then multiplies all groups by the column tiles
+// ct = wave, wave + 4, ..  With H as operand A a lane ends up with four
+// consecutive elements of one group per tile, so the Walsh-Hadamard bits 0-3
+// of the group index are DPP butterflies across 16 lanes and bits 4.. run in
+// the lane's own registers: the rotated row never leaves them.  Codes go
+// through LDS once, to be stored as whole lines.
+//
+// The digit kernel above spends about 94 VALU instructions per element, most
+// of them on its 7-digit planes and the binary64 sums of 4 products per
+// output; the split takes 5 and the sum 1.  7B down projection input
+// (2048 x 11008, SwiGLU): 109 -> 71 us; 517 x 13824, int8 codes: 34 -> 20 us.
+// What is left is mostly the SiLU (about 30 instructions per element) and the
+// quantizer.  Six or eight waves per block were slower (108 us; 24 us): they
+// leave one block per CU.
+template <int M, int RT, int EPI, int PRO>
+__global__ __launch_bounds__(256, 2) void k_rot_largem_f16(RotArgs a)
+{
+    typedef LargemLds<M, RT, EPI> Z;
+    constexpr int W = 4, CT = HmF16A<M>::CT, KB = HmF16A<M>::KB;
+    constexpr int CTW = (CT + W - 1) / W;  // column tiles per wave
+    constexpr int N = Z::N, ITEMS = RT * KB, IPW = (ITEMS + W - 1) / W;
+    extern __shared__ __align__(16) uint8_t lds[];
+    __shared__ float red[W];
+    __shared__ int big[W];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int pos = lane_pos(lane) & 15, quad = lane >> 4;
+
+    // Item it = rt KB + kb: inputs b = kb*32 + (l/16)*8 + e of group
+    // rt*16 + pos, in lane l's half e.  Past the group's end H holds zeros,
+    // so any input of the row will do.  A wave takes items wave, wave + W, ..;
+    // the next row's are read while this row's are multiplied, unless the
+    // row has eight tiles, whose outputs leave no registers for them.
+    constexpr bool AHEAD = RT < 8;
+    constexpr int OPS = PRO == PRO_SWIGLU ? 2 : 1;
+    uint2 raw[OPS][IPW][2];
+    auto load_row = [&](int64_t row) {
+        const uint16_t *src[2] = {a.x + row * N, PRO == PRO_SWIGLU ? a.x2 + row * N : nullptr};
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+            const int it = min(wave + W * j, ITEMS - 1);
+            const int off = (it / KB * 16 + pos) * M + it % KB * 32 + quad * 8;
+#pragma unroll
+            for (int o = 0; o < OPS; ++o) {
+                raw[o][j][0] = *reinterpret_cast<const uint2 *>(src[o] + min(off, N - 4));
+                raw[o][j][1] = *reinterpret_cast<const uint2 *>(src[o] + min(off + 4, N - 4));
+            }
+        }
+    };
+    if (AHEAD)
+        load_row(blockIdx.x);
+
+    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+        if (!AHEAD)
+            load_row(row);
+        // this wave's items, in registers until the whole block knows
+        // whether a value of 512 or more is among them
+        uint32_t t[IPW][4], wide = 0;  // bits 14 and 30 of wide: one was seen
+#pragma unroll
+        for (int j = 0; j < IPW; ++j)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                auto word = [&](int o) {
+                    const uint2 r = raw[o][j][p >> 1];
+                    return p & 1 ? r.y : r.x;
+                };
+                if constexpr (PRO == PRO_PLAIN) {
+                    t[j][p] = word(0);
+                } else {
+                    const uint32_t g = word(0), u = word(1);
+                    t[j][p] = (uint32_t)f2h(silu_f32(h2f((uint16_t)g)) * h2f((uint16_t)u)) |
+                              ((uint32_t)f2h(silu_f32(h2f((uint16_t)(g >> 16))) *
+                                             h2f((uint16_t)(u >> 16)))
+                               << 16);
+                }
+                wide |= t[j][p] & (t[j][p] << 1);  // exponent bits 14 and 13 both set
+            }
+        if (AHEAD && row + gridDim.x < a.rows)
+            load_row(row + gridDim.x);
+        const bool any = __any((wide & 0x40004000u) != 0);
+        if (lane == 0)
+            big[wave] = any;
+        __syncthreads();
+        int row_wide = 0;
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+            row_wide |= big[i];
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+            const int it = wave + W * j;
+            if (ITEMS % W != 0 && it >= ITEMS)
+                continue;
+            uint4 hv, lv;
+            uint32_t *hw = &hv.x, *lw = &lv.x;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                v2h h, l;
+                f16_split(__builtin_bit_cast(v2h, t[j][p]), h, l);
+                hw[p] = row_wide ? t[j][p] : __builtin_bit_cast(uint32_t, h);
+                lw[p] = __builtin_bit_cast(uint32_t, l);
+            }
+            *reinterpret_cast<uint4 *>(lds + (it * 64 + lane) * 16) = hv;
+            *reinterpret_cast<uint4 *>(lds + Z::PLANE + (it * 64 + lane) * 16) = lv;
+        }
+        // this wave's H operands: loaded for each row (from the caches, behind
+        // an index the compiler cannot see through), since held from row to
+        // row they would push the splits' registers out
+        int fresh = 0;
+        __asm__("" : "+s"(fresh));
+        const uint4 *hsrc = hm_f16_a<M>() + fresh + lane;
+        v8h H[CTW][KB];
+#pragma unroll
+        for (int i = 0; i < CTW; ++i)
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+                H[i][kb] = __builtin_bit_cast(
+                    v8h, hsrc[(min(wave + W * i, CT - 1) * KB + kb) * 64]);
+        __syncthreads();
+
+        // u (times 2^7) of this wave's column tiles: lane l holds columns
+        // ct*16 + 4 (l/16) + r of group rt*16 + pos in v[i][rt][r]
+        float v[CTW][RT][4];
+        auto plane = [&](int p, int rt, int kb) {
+            return *reinterpret_cast<const v8h *>(lds + p * Z::PLANE +
+                                                  ((rt * KB + kb) * 64 + lane) * 16);
+        };
+        if (!row_wide) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                v4f sh[CTW], sl[CTW];
+#pragma unroll
+                for (int i = 0; i < CTW; ++i)
+                    sh[i] = sl[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) {
+                    const v8h hv = plane(0, rt, kb), lv = plane(1, rt, kb);
+#pragma unroll
+                    for (int i = 0; i < CTW; ++i) {
+                        sh[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H[i][kb], hv, sh[i], 0, 0, 0);
+                        sl[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(H[i][kb], lv, sl[i], 0, 0, 0);
+                    }
+                }
+                // both sums are exact, so this fma's is the one rounding
+#pragma unroll
+                for (int i = 0; i < CTW; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        v[i][rt][r] = __builtin_fmaf(sl[i][r], 0x1p-10f, sh[i][r]);
+            }
+        } else {
+            // A value of 512 or more somewhere in the row: the plane holds t
+            // itself; t = h1 + t1 with h1 = rint(t) (exact in fp16) and
+            // |t1| <= 1/2 split as above.  The three exact sums meet in
+            // binary64 (multiples of 2^-17 below 2^31).
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                v4f s1[CTW], sh[CTW], sl[CTW];
+#pragma unroll
+                for (int i = 0; i < CTW; ++i)
+                    s1[i] = sh[i] = sl[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+                for (int kb = 0; kb < KB; ++kb) {
+                    const v8h tv = plane(0, rt, kb);
+                    const v8h h1 = __builtin_elementwise_rint(tv);
+                    v8h hv, lv;
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) {
+                        v2h h, l;
+                        f16_split(v2h{tv[2 * p] - h1[2 * p], tv[2 * p + 1] - h1[2 * p + 1]}, h, l);
+                        hv[2 * p] = h[0], hv[2 * p + 1] = h[1];
+                        lv[2 * p] = l[0], lv[2 * p + 1] = l[1];
+                    }
+#pragma unroll
+                    for (int i = 0; i < CTW; ++i) {
+                        // (from the table: H is indexed at compile time)
+                        const v8h Hk = __builtin_bit_cast(
+                            v8h, hsrc[(min(wave + W * i, CT - 1) * KB + kb) * 64]);
+                        s1[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, h1, s1[i], 0, 0, 0);
+                        sh[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, hv, sh[i], 0, 0, 0);
+                        sl[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, lv, sl[i], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < CTW; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        v[i][rt][r] = (float)__builtin_fma(
+                            (double)sl[i][r], 0x1p-10,
+                            __builtin_fma((double)s1[i][r], 128.0, (double)sh[i][r]));
+            }
+        }
+
+        // group bits 0-3 across lanes, 4.. in registers
+        const float sigma = lane_stages<4, CTW * RT * 4>(&v[0][0][0], lane, pos);
+#pragma unroll
+        for (int h = 1; h < RT; h <<= 1)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+                if (!(rt & h)) {
+#pragma unroll
+                    for (int i = 0; i < CTW; ++i)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float p = v[i][rt][r], q = v[i][rt + h][r];
+                            v[i][rt][r] = p + q;
+                            v[i][rt + h][r] = p - q;
+                        }
+                }
+        // c times the power of two the sums carry, and the lane's sign
+        const float sc = sigma * (a.c * 0x1p-7f);
+        auto each = [&](auto &&f) {  // f(element offset, the 4 values there)
+#pragma unroll
+            for (int i = 0; i < CTW; ++i) {
+                const int b0 = (wave + W * i) * 16 + 4 * quad;
+                if (b0 >= M)
+                    continue;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    f((rt * 16 + pos) * M + b0, v[i][rt]);
+            }
+        };
+        if constexpr (EPI == EPI_F32) {
+            each([&](int off, float *y) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    y[r] = __builtin_fmaf(y[r], sc, 0.0f);  // zeros +0
+                store_y4<EPI_F32>(a.out, row * N + off, y);
+            });
+        } else if constexpr (EPI == EPI_F16) {
+            __syncthreads();  // the planes were read
+            each([&](int off, float *y) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    y[r] = __builtin_fmaf(y[r], sc, 0.0f);
+                store4(reinterpret_cast<uint16_t *>(lds) + off, y);
+            });
+            __syncthreads();
+            uint4 *dst = reinterpret_cast<uint4 *>(static_cast<uint16_t *>(a.out) + row * N);
+            for (int c = tid; c < N / 8; c += 64 * W)
+                dst[c] = reinterpret_cast<const uint4 *>(lds)[c];
+        } else {
+            float amax = 0.0f;
+            each([&](int, float *y) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    y[r] = y[r] * sc;
+                    amax = fmaxf(amax, fabsf(y[r]));
+                }
+            });
+            static_for<6>([&](auto J) { amax = lane_max<J>(amax); });
+            if (lane == 0)
+                red[wave] = amax;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < W; ++i)
+                amax = fmaxf(amax, red[i]);
+            const float qd = sym_divisor<EPI>(a);
+            const uint16_t s16 = f2h((amax * a.clip) / qd);
+            const Divisor dv = make_divisor(h2f(s16));
+            constexpr int CODES = EPI == EPI_SYM ? EPI_SYM : EPI_SYM8;
+            each([&](int off, float *y) { store_codes4<CODES>(lds, off, y, dv, qd); });
+            __syncthreads();
+            if constexpr (EPI == EPI_E3M2) {
+                // whole units of 32 codes through one fp6 pack conversion, as
+                // in k_rot_smallm
+                uint8_t *q = static_cast<uint8_t *>(a.out);
+                for (int u = tid; u < N / 32; u += 64 * W) {
+                    const uint4 in0 = reinterpret_cast<const uint4 *>(lds)[2 * u];
+                    const uint4 in1 = reinterpret_cast<const uint4 *>(lds)[2 * u + 1];
+                    const uint32_t wd[8] = {in0.x, in0.y, in0.z, in0.w,
+                                            in1.x, in1.y, in1.z, in1.w};
+                    v16f ev, od;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        ev[2 * k] = (float)(int8_t)(wd[k] & 0xFFu);
+                        od[2 * k] = (float)(int8_t)((wd[k] >> 8) & 0xFFu);
+                        ev[2 * k + 1] = (float)(int8_t)((wd[k] >> 16) & 0xFFu);
+                        od[2 * k + 1] = (float)(int8_t)(wd[k] >> 24);
+                    }
+                    const v6i o = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(ev, od, 1.0f);
+                    *reinterpret_cast<uint4 *>(q + e3m2_head(a.rows, row, u >> 2, u & 3)) =
+                        make_uint4((uint32_t)o[0], (uint32_t)o[1], (uint32_t)o[2], (uint32_t)o[3]);
+                    *reinterpret_cast<uint2 *>(q + e3m2_tail(a.rows, row, u >> 2, u & 3)) =
+                        make_uint2((uint32_t)o[4], (uint32_t)o[5]);
+                }
+            } else {
+                constexpr int BYTES = EPI == EPI_SYM ? N / 2 : N;
+                uint4 *dst = reinterpret_cast<uint4 *>(static_cast<uint8_t *>(a.out) +
+                                                       row * BYTES);
+                for (int c = tid; c < BYTES / 16; c += 64 * W)
+                    dst[c] = reinterpret_cast<const uint4 *>(lds)[c];
+            }
+            if (tid == 0)
+                a.scale[row] = s16;
+        }
+        __syncthreads();  // the next row's planes overwrite what was read here
+    }
+}
+
 // ------------------------------------------------- no rotation, any n -----
 
 template <int EPI>
@@ -1514,9 +1883,34 @@ hipError_t go_smallm(const RotArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int M, int RT, int EPI, int PRO>
+hipError_t go_largem_f16(const RotArgs &a, hipStream_t s)
+{
+    constexpr int lds = LargemLds<M, RT, EPI>::BYTES;
+    const void *fn = (const void *)k_rot_largem_f16<M, RT, EPI, PRO>;
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess)
+        return e;
+    // 512 blocks are resident (two per CU); a block takes the same number of
+    // rows as any other, give or take one
+    const int64_t per = (a.rows + 511) / 512, grid = (a.rows + per - 1) / per;
+    hipLaunchKernelGGL((k_rot_largem_f16<M, RT, EPI, PRO>), dim3((unsigned)grid), dim3(256), lds, s,
+                       a);
+    return hipGetLastError();
+}
+
 template <int M, int EPI, int PRO>
 hipError_t go_largem(const RotArgs &a, hipStream_t s)
 {
+    switch (a.n / M) {
+    case 16: return go_largem_f16<M, 1, EPI, PRO>(a, s);
+    case 32: return go_largem_f16<M, 2, EPI, PRO>(a, s);
+    case 64: return go_largem_f16<M, 4, EPI, PRO>(a, s);
+    case 128:
+        if constexpr (M == 108)
+            return go_largem_f16<M, 8, EPI, PRO>(a, s);
+        return hipErrorInvalidValue;
+    }
     // H_M's operand tiles, then the staged row
     const size_t lds = (size_t)HmMfmaB<M>::CT * HmMfmaB<M>::KB * 1024 +
                        (size_t)a.n * sizeof(float);
