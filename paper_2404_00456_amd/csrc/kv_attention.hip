@@ -284,20 +284,28 @@ typedef _Float16 h2v __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // The nibbles at bits 4-7 and 20-23 need no shift: or-ed into 0x5400 (64,
-// spacing 1/16) they read 64 + c.  The and-or is one v_and_or_b32 on
-// register operands (gfx9 VOP3 takes no literal, and the compiler otherwise
-// splits it into an and and an or).
+// spacing 1/16) they read 64 + c.  The and-or becomes one v_and_or_b32 on
+// register operands (gfx9 VOP3 takes no literal, and with constants in sight
+// the compiler splits it into an and and an or), so the constants pass
+// through an empty asm once.  The instruction itself is left to the compiler:
+// its output may take a register that a matrix instruction in flight still
+// writes (the unused rows of a score), and only for its own instructions does
+// the compiler put the wait states between.
 struct NibConst {
     uint32_t mlo, mhi, glo, ghi;  // masks and magic exponents, in registers
 };
 
+__device__ __forceinline__ NibConst nib_const()
+{
+    NibConst k = {0x000F000Fu, 0x00F000F0u, 0x64006400u, 0x54005400u};
+    __asm__("" : "+v"(k.mlo), "+v"(k.mhi), "+v"(k.glo), "+v"(k.ghi));
+    return k;
+}
+
 template <bool HI>
 __device__ __forceinline__ h2v nib_pair(uint32_t w, const NibConst &k)
 {
-    uint32_t x;
-    __asm__("v_and_or_b32 %0, %1, %2, %3"
-            : "=v"(x)
-            : "v"(w), "v"(HI ? k.mhi : k.mlo), "v"(HI ? k.ghi : k.glo));
+    const uint32_t x = (w & (HI ? k.mhi : k.mlo)) | (HI ? k.ghi : k.glo);
     const _Float16 b = HI ? (_Float16)-64.0f : (_Float16)-1024.0f;
     const h2v off = {b, b};
     return __builtin_bit_cast(h2v, x) + off;
@@ -356,7 +364,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
     for (int dc = 0; dc < 8; ++dc)
         orun[dc] = 0.0f;
     float m = -inf, l = 0.0f, zs = 0.0f;
-    const NibConst nk = {0x000F000Fu, 0x00F000F0u, 0x64006400u, 0x54005400u};
+    const NibConst nk = nib_const();
     // this cache row block's codes and constants: wave-uniform bases, 32-bit
     // offsets (s_max * 64 bytes < 2^32)
     const int64_t rbase = kvr * a.s_max;
