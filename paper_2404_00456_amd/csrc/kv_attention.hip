@@ -16,7 +16,8 @@
 // with several chunks the partial (max, sum, o) go to a workspace and a
 // second kernel combines them.  Groups must be at least 32 wide, so that a
 // lane's 32 elements share one scale and zero.  Head_dim 128 with one group
-// per row takes the matrix-core kernel further below instead.
+// per row takes the matrix-core kernels further below instead, one for a
+// query row per cache row and one for several, with 8 waves in a block.
 #include <algorithm>
 
 #include "common.hpp"
@@ -101,7 +102,7 @@ __device__ __forceinline__ void axpy_codes(const uint4 &c, float w, float *o)
 // wave left its running maximum, its sum of weights and its unnormalized
 // output (zero-point term included) in red[w].  The result is the output
 // row, or the split's partial (max, sum, o).
-template <int D>
+template <int D, int NW>
 __device__ __forceinline__ void combine_waves(const KvAttnArgs &a, const float (*red)[D + 2],
                                               int64_t qi, int split, int tid)
 {
@@ -109,12 +110,12 @@ __device__ __forceinline__ void combine_waves(const KvAttnArgs &a, const float (
     if (tid < D) {
         float mx = red[0][0];
 #pragma unroll
-        for (int w = 1; w < ATT_WAVES; ++w)
+        for (int w = 1; w < NW; ++w)
             mx = fmaxf(mx, red[w][0]);
         float lt = 0.0f, ot = 0.0f;
         if (mx > -inf) {
 #pragma unroll
-            for (int w = 0; w < ATT_WAVES; ++w) {
+            for (int w = 0; w < NW; ++w) {
                 const float f = __expf(red[w][0] - mx);  // 0 for an empty wave
                 lt = __builtin_fmaf(red[w][1], f, lt);
                 ot = __builtin_fmaf(red[w][2 + tid], f, ot);
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn(KvAttnArgs a)
         }
     }
     __syncthreads();
-    combine_waves<D>(a, red, qi, split, tid);
+    combine_waves<D, ATT_WAVES>(a, red, qi, split, tid);
 }
 
 // ---- head_dim 128 with one scale and zero per cached row: on the matrix
@@ -265,14 +266,14 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn(KvAttnArgs a)
 // row is then the token's dot product, exact up to the binary32
 // accumulation.
 //
-// Values: v_mfma_f32_16x16x16_f16 with A = the tokens' weights p_t vs_t
-// rounded to fp16 (every row the same) and B = the V codes, contracting over
-// the 16 tokens.  Lane l loads code bytes 4 n .. 4 n + 3 (elements
-// 8 n .. 8 n + 7) of tokens 4 g .. 4 g + 3, and output column n of step
-// dc = 0..7 accumulates element 8 n + dc.  The weights' fp16 rounding
-// (relative 2^-11, like that of the fp16 output) is the only change from
-// the vector kernel's arithmetic; the zero-point term sum_t p_t vz_t and
-// the softmax sums stay in binary32.
+// Values: v_mfma_f32_16x16x16_f16 with A = the tokens' weights p_t vs_t and
+// B = the V codes, contracting over the 16 tokens.  Of the 16 rows of A, eight
+// hold the weights' fp16 values and eight the fp16 rests, so that the sum of
+// two output rows keeps 22 bits of each weight at no further matrix
+// instruction.  Lane l loads code bytes 4 n .. 4 n + 3 (elements 8 n .. 8 n +
+// 7) of tokens 4 g .. 4 g + 3, and output column n of step dc = 0..7
+// accumulates element 8 n + dc.  The zero-point term sum_t p_t vz_t and the
+// softmax sums stay in binary32.
 //
 // A code c becomes an fp16 integer by or-ing it into the significand of a
 // 16-bit lane holding 1024 (where fp16 values are spaced by 1), giving
@@ -316,12 +317,28 @@ __device__ __forceinline__ _Float16 bits_h(uint32_t b)
     return __builtin_bit_cast(_Float16, (uint16_t)b);
 }
 
+// w as fp16 in the low half and the fp16 rest in the high one (w's 22 leading
+// bits together; infinities stay what they are)
+__device__ __forceinline__ uint32_t split_h(float w)
+{
+    const _Float16 hi = (_Float16)w;
+    const float f = (float)hi;
+    const _Float16 lo = (_Float16)(f < __builtin_inff() ? w - f : f);
+    return (uint32_t)__builtin_bit_cast(uint16_t, hi) |
+           ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
+}
+
 constexpr int MFMA_U = 4;  // 16-token groups per wave per iteration
 
-__global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
+// NW waves share a row's tokens.  Eight keep enough loads in flight for a row
+// to be read whole by one block: 16 x 32 rows of 2047 tokens (143 MB) take
+// 30.2 us, against 37.6 with four waves and four blocks per row.  Sixteen
+// gained nothing (32.6).  The read is what bounds it then (4.7 TB/s).
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_kv_attn_mfma(KvAttnArgs a)
 {
     constexpr int D = 128;
-    __shared__ float red[ATT_WAVES][D + 2];
+    __shared__ float red[NW][D + 2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
     const int64_t qi = blockIdx.x;
@@ -364,6 +381,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
     for (int dc = 0; dc < 8; ++dc)
         orun[dc] = 0.0f;
     float m = -inf, l = 0.0f, zs = 0.0f;
+    // the high or the low halves of two words
+    const uint32_t half = n < 8 ? 0x05040100u : 0x07060302u;
     const NibConst nk = nib_const();
     // this cache row block's codes and constants: wave-uniform bases, 32-bit
     // offsets (s_max * 64 bytes < 2^32)
@@ -372,7 +391,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
     const uint16_t *ksb = a.ks + rbase, *kzb = a.kz + rbase, *vsb = a.vs + rbase, *vzb = a.vz + rbase;
 
     for (int base = t_begin + wave * 16 * MFMA_U; base < t_end;
-         base += ATT_WAVES * 16 * MFMA_U) {
+         base += NW * 16 * MFMA_U) {
         uint4 kc[MFMA_U];
         uint32_t vw[MFMA_U][4];
         float ksc[MFMA_U], kze[MFMA_U], vsc[MFMA_U], vze[MFMA_U];
@@ -414,8 +433,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
         }
         // over the 16 tokens of a row (the four rows hold the same tokens)
         static_for<4>([&](auto J) { tmax = lane_max<J>(tmax); });
-        const float mn = fmaxf(m, tmax);  // finite: every iteration has a token
-        if (mn > m) {                     // uniform across the wave
+        const float mn = fmaxf(m, tmax);
+        if (mn > m) {  // uniform across the wave
             const float alpha = __expf(m - mn);
 #pragma unroll
             for (int dc = 0; dc < 8; ++dc)
@@ -424,19 +443,23 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
             zs *= alpha;
             m = mn;
         }
+        const float ms = m > -inf ? m : 0.0f;  // no finite score so far: weights 0
         v4f o[8];
 #pragma unroll
         for (int u = 0; u < MFMA_U; ++u) {
-            const float p = __expf(sc[u] - m);  // 0 for masked tokens
+            const float p = __expf(sc[u] - ms);  // 0 for masked tokens
             l += p;
             zs = __builtin_fmaf(p, vze[u], zs);
-            const float wt = p * vsc[u];
             // A operand: the weights of tokens 4 g .. 4 g + 3 (lanes
-            // 16 g + 4 g + j of this row)
-            v4h av;
+            // 16 g + 4 g + j of this row), rows 0 .. 7 their fp16 values and
+            // rows 8 .. 15 what those leave
+            const uint32_t wt = split_h(p * vsc[u]);
+            uint32_t w[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                av[j] = (_Float16)__shfl(wt, 20 * g + j);
+                w[j] = __shfl(wt, 20 * g + j);
+            const v4h av = __builtin_bit_cast(v4h, make_uint2(perm_b32(w[1], w[0], half),
+                                                              perm_b32(w[3], w[2], half)));
 #pragma unroll
             for (int bt = 0; bt < 4; ++bt) {
                 // byte bt of tokens 4 g, 4 g + 1 (and + 2, + 3) in bytes 0, 2
@@ -458,11 +481,14 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
             orun[dc] += o[dc][0];
     }
 
-    // sums over the 16 tokens of a row
+    // sums over the 16 tokens of a row; output rows 0 and 8
     static_for<4>([&](auto J) {
         l = lane_sum<J>(l);
         zs = lane_sum<J>(zs);
     });
+#pragma unroll
+    for (int dc = 0; dc < 8; ++dc)
+        orun[dc] = lane_sum<5>(orun[dc]);
     if (g == 0) {
 #pragma unroll
         for (int dc = 0; dc < 8; ++dc)
@@ -473,26 +499,246 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn_mfma(KvAttnArgs a)
         }
     }
     __syncthreads();
-    combine_waves<D>(a, red, qi, split, tid);
+    combine_waves<D, NW>(a, red, qi, split, tid);
+}
+
+// ---- the same with up to 8 query rows sharing a cache row (grouped-query
+// attention): the cache is read once for all of them, where a block per query
+// row reads and unpacks it rep times.  Past 8 rows a cache row takes several
+// blocks.  40 cache rows of 8 queries over 4099 tokens: 14.8 us with the
+// combining pass, 37 as 320 blocks of one query each; 192 x 8 over 3000
+// tokens (78 MB): 28.6 us.  What bounds the long ones is the
+// unpacking (two vector instructions per code pair, K and V), the short ones
+// the chain of one load, two matrix products and a reduction per 32 tokens.
+//
+// Scores: A = the K codes (16 tokens), B = the queries (columns n and n + 8
+// query n; past R the last one), so lane l gets query l % 8 against tokens
+// 4 g + r (r = 0..3, g = l / 16), which is how the values' A operand wants the
+// weights: row n, contraction index 4 g + j; rows 0 .. 7 hold their fp16
+// values and rows 8 .. 15 what those leave.  Values: the output holds query
+// (4 g + r) % 8, element 8 n + dc, accumulated in the matrix registers over
+// all of the wave's tokens; the running maxima are per query (per lane), and
+// when one grows the accumulators are rescaled by factors fetched across
+// lanes.
+constexpr int GQA_R = 8;  // query rows per block
+constexpr int GQA_U = 2;  // 16-token groups per wave per iteration
+
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_kv_attn_gqa(KvAttnArgs a)
+{
+    constexpr int D = 128;
+    extern __shared__ __align__(16) float gred[];  // [NW][R][D + 2]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 15, g = lane >> 4;
+    const int per = (a.rep + GQA_R - 1) / GQA_R;  // blocks per cache row
+    const int64_t kvr = blockIdx.x / per;
+    const int r0 = (int)(blockIdx.x % per) * GQA_R, R = min(GQA_R, a.rep - r0);
+    const int64_t q0 = kvr * a.rep + r0;
+    const int split = blockIdx.y;
+    const int t_begin = split * a.chunk;
+    const int t_end = min(a.seq_len, t_begin + a.chunk);
+    const float inf = __builtin_inff();
+
+    v8h qb[4];
+    float qsum = 0.0f;
+    {
+        const uint4 *qr = reinterpret_cast<const uint4 *>(a.q + (q0 + min(n & 7, R - 1)) * D + 32 * g);
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc) {
+            const uint4 raw = qr[kc];
+            const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+            _Float16 e[8];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                e[2 * i] = bits_h(w[i] & 0xFFFFu);
+                e[2 * i + 1] = bits_h(w[i] >> 16);
+            }
+            qb[kc] = v8h{e[0], e[4], e[1], e[5], e[2], e[6], e[3], e[7]};
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                qsum += (float)e[i];
+        }
+        qsum = lane_sum<4>(qsum);
+        qsum = lane_sum<5>(qsum);
+    }
+
+    v4f o[8];
+#pragma unroll
+    for (int dc = 0; dc < 8; ++dc)
+        o[dc] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    float m = -inf, l = 0.0f, zs = 0.0f;
+    const uint32_t half = n < 8 ? 0x05040100u : 0x07060302u;
+    const NibConst nk = nib_const();
+    const int64_t rbase = kvr * a.s_max;
+    const uint8_t *kcb = a.kc + rbase * (D / 2), *vcb = a.vc + rbase * (D / 2);
+    const uint16_t *ksb = a.ks + rbase, *kzb = a.kz + rbase, *vsb = a.vs + rbase, *vzb = a.vz + rbase;
+
+    for (int base = t_begin + wave * 16 * GQA_U; base < t_end; base += NW * 16 * GQA_U) {
+        uint4 kc[GQA_U];
+        uint32_t vw[GQA_U][4];
+        uint16_t ksc[GQA_U][4], kze[GQA_U][4], vsc[GQA_U][4], vze[GQA_U][4];
+#pragma unroll
+        for (int u = 0; u < GQA_U; ++u) {
+            const int t0 = base + 16 * u;
+            const uint32_t row = (uint32_t)min(t0 + n, t_end - 1);
+            kc[u] = *reinterpret_cast<const uint4 *>(kcb + (row * (D / 2) + 16 * g));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t rj = (uint32_t)min(t0 + 4 * g + j, t_end - 1);
+                vw[u][j] = *reinterpret_cast<const uint32_t *>(vcb + (rj * (D / 2) + 4 * n));
+                ksc[u][j] = ksb[rj];
+                kze[u][j] = kzb[rj];
+                vsc[u][j] = vsb[rj];
+                vze[u][j] = vzb[rj];
+            }
+        }
+        float sc[GQA_U][4];
+        float tmax = -inf;
+#pragma unroll
+        for (int u = 0; u < GQA_U; ++u) {
+            v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+            const uint32_t w4[4] = {kc[u].x, kc[u].y, kc[u].z, kc[u].w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t w8 = w4[k] >> 8;
+                const h2v p0 = nib_pair<false>(w4[k], nk), p1 = nib_pair<true>(w4[k], nk);
+                const h2v p2 = nib_pair<false>(w8, nk), p3 = nib_pair<true>(w8, nk);
+                const v8h b = {p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(b, qb[k], acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float s = __builtin_fmaf(h2f(ksc[u][j]), acc[j], h2f(kze[u][j]) * qsum);
+                sc[u][j] = base + 16 * u + 4 * g + j < t_end ? s * a.sm_scale : -inf;
+                tmax = fmaxf(tmax, sc[u][j]);
+            }
+        }
+        // over the lane groups (16 GQA_U tokens of this lane's query)
+        tmax = lane_max<4>(tmax);
+        tmax = lane_max<5>(tmax);
+        const float mn = fmaxf(m, tmax);
+        const float ms = mn > -inf ? mn : 0.0f;  // no finite score so far: weights 0
+        if (__any(mn > m)) {
+            const float alpha = __expf(m - ms);  // 0 on the first iteration
+            l *= alpha;
+            zs *= alpha;
+            m = mn;
+            float f[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                f[r] = __shfl(alpha, 4 * g + r);
+#pragma unroll
+            for (int dc = 0; dc < 8; ++dc)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    o[dc][r] *= f[r];
+        }
+#pragma unroll
+        for (int u = 0; u < GQA_U; ++u) {
+            uint32_t w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float p = __expf(sc[u][j] - ms);  // 0 for masked tokens
+                l += p;
+                zs = __builtin_fmaf(p, h2f(vze[u][j]), zs);
+                w[j] = split_h(p * h2f(vsc[u][j]));
+            }
+            const v4h av = __builtin_bit_cast(v4h, make_uint2(perm_b32(w[1], w[0], half),
+                                                              perm_b32(w[3], w[2], half)));
+#pragma unroll
+            for (int bt = 0; bt < 4; ++bt) {
+                const uint32_t sel = (uint32_t)bt | 0x0C00u | ((uint32_t)(4 + bt) << 16) | 0x0C000000u;
+                const uint32_t x01 = perm_b32(vw[u][1], vw[u][0], sel);
+                const uint32_t x23 = perm_b32(vw[u][3], vw[u][2], sel);
+                const h2v lo01 = nib_pair<false>(x01, nk), lo23 = nib_pair<false>(x23, nk);
+                const h2v hi01 = nib_pair<true>(x01, nk), hi23 = nib_pair<true>(x23, nk);
+                const v4h blo = {lo01[0], lo01[1], lo23[0], lo23[1]};
+                const v4h bhi = {hi01[0], hi01[1], hi23[0], hi23[1]};
+                o[2 * bt] = __builtin_amdgcn_mfma_f32_16x16x16f16(av, blo, o[2 * bt], 0, 0, 0);
+                o[2 * bt + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(av, bhi, o[2 * bt + 1], 0, 0, 0);
+            }
+        }
+    }
+
+    // over the lane groups; then every wave's (max, sum, o) per query in LDS
+    l = lane_sum<5>(lane_sum<4>(l));
+    zs = lane_sum<5>(lane_sum<4>(zs));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int qr = 4 * (g & 1) + r;
+        const float z = __shfl(zs, qr);
+#pragma unroll
+        for (int dc = 0; dc < 8; ++dc)
+            o[dc][r] = lane_sum<5>(o[dc][r]) + z;  // output rows qr and qr + 8
+        if (g < 2 && qr < R) {
+            float *dst = gred + (wave * R + qr) * (D + 2) + 2 + 8 * n;
+#pragma unroll
+            for (int dc = 0; dc < 8; ++dc)
+                dst[dc] = o[dc][r];
+        }
+    }
+    if (g == 0 && n < R) {
+        float *dst = gred + (wave * R + n) * (D + 2);
+        dst[0] = m;
+        dst[1] = l;
+    }
+    __syncthreads();
+    for (int i = tid; i < R * D; i += 64 * NW) {
+        const int qr = i / D, d = i % D;
+        const float *src = gred + qr * (D + 2);
+        float mx = -inf;
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            mx = fmaxf(mx, src[w * R * (D + 2)]);
+        float lt = 0.0f, ot = 0.0f;
+        if (mx > -inf) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float f = __expf(src[w * R * (D + 2)] - mx);  // 0 for an empty wave
+                lt = __builtin_fmaf(src[w * R * (D + 2) + 1], f, lt);
+                ot = __builtin_fmaf(src[w * R * (D + 2) + 2 + d], f, ot);
+            }
+        }
+        const int64_t qi = q0 + qr;
+        if (a.splits == 1) {
+            a.out[qi * D + d] = f2h(ot / lt);
+        } else {
+            float *pp = a.part + (qi * a.splits + split) * (D + 2);
+            if (d == 0) {
+                pp[0] = mx;
+                pp[1] = lt;
+            }
+            pp[2 + d] = ot;
+        }
+    }
 }
 
 // out[qi][d] from the splits' (max, sum, o): one block of D threads per row.
+// The maxima and sums come in by one load per thread; read one after the
+// other they cost a memory latency per split (64 rows x 32 splits: 16 us).
+constexpr int MAX_SPLITS = 2048;  // kv_attn_splits(1, ..)
+
 template <int D>
 __global__ __launch_bounds__(D) void k_kv_attn_combine(KvAttnArgs a)
 {
+    __shared__ float ms[MAX_SPLITS], ls[MAX_SPLITS];
     const int64_t qi = blockIdx.x;
     const int d = threadIdx.x;
     const float *pp = a.part + qi * a.splits * (D + 2);
+    for (int s = d; s < a.splits; s += D) {
+        const float2 v = *reinterpret_cast<const float2 *>(pp + s * (D + 2));
+        ms[s] = v.x;
+        ls[s] = v.y;
+    }
+    __syncthreads();
     float mx = -__builtin_inff();
     for (int s = 0; s < a.splits; ++s)
-        mx = fmaxf(mx, pp[s * (D + 2)]);
+        mx = fmaxf(mx, ms[s]);
     float lt = 0.0f, ot = 0.0f;
+#pragma unroll 8
     for (int s = 0; s < a.splits; ++s) {
-        const float ms = pp[s * (D + 2)];
-        if (ms == -__builtin_inff())
-            continue;  // an empty chunk
-        const float f = __expf(ms - mx);
-        lt = __builtin_fmaf(pp[s * (D + 2) + 1], f, lt);
+        const float f = __expf(ms[s] - mx);  // 0 for an empty chunk, whose o is 0
+        lt = __builtin_fmaf(ls[s], f, lt);
         ot = __builtin_fmaf(pp[s * (D + 2) + 2 + d], f, ot);
     }
     a.out[qi * D + d] = f2h(ot / lt);
@@ -510,10 +756,37 @@ hipError_t go_attn(const KvAttnArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t go_attn_mfma(const KvAttnArgs &a, hipStream_t s)
+// How many blocks share a cache row's tokens on the matrix path: at most the
+// workspace's a.splits, and one wave of blocks over the 256 compute units,
+// eight waves in each.  More blocks than that read no faster and the partial
+// results cost a second launch and a pass (16 x 32 rows, 2047 tokens: 30.2 us
+// whole, 33.0 in two, 36.6 in four; 40 rows of 8 queries, 4099 tokens: 35.1
+// whole, 16.7 in four, 14.8 in six, 19.4 in sixteen).  That pass costs as much
+// as reading some 600 tokens, so a row is left whole unless splitting takes
+// off more (32 rows: 600 tokens 5.7 whole, 6.4 split; 800 tokens 7.0, 6.3;
+// 128 rows: 1000 tokens 7.9 whole, 9.0 in two; 1300 tokens 10.1, 9.8).
+int mfma_splits(const KvAttnArgs &a, int64_t blocks)
 {
-    hipLaunchKernelGGL(k_kv_attn_mfma, dim3((unsigned)a.nq, (unsigned)a.splits),
-                       dim3(64 * ATT_WAVES), 0, s, a);
+    const int64_t f = 256 / blocks;
+    if (f < 2 || (int64_t)a.seq_len * (f - 1) <= 600 * f)
+        return 1;
+    return (int)std::min<int64_t>(a.splits, f);
+}
+
+template <int NW>
+hipError_t go_attn_mfma(KvAttnArgs a, hipStream_t s)
+{
+    const int per = (a.rep + GQA_R - 1) / GQA_R, R = std::min(GQA_R, a.rep);
+    const int64_t blocks = a.rep == 1 ? a.nq : a.nq / a.rep * per;
+    a.splits = mfma_splits(a, blocks);
+    a.chunk = (int)((((int64_t)a.seq_len + a.splits - 1) / a.splits + 63) / 64 * 64);
+    const dim3 grid((unsigned)blocks, (unsigned)a.splits);
+    if (a.rep == 1) {
+        hipLaunchKernelGGL(k_kv_attn_mfma<NW>, grid, dim3(64 * NW), 0, s, a);
+    } else {
+        const int lds = NW * R * (128 + 2) * 4;  // at most 33 KB
+        hipLaunchKernelGGL(k_kv_attn_gqa<NW>, grid, dim3(64 * NW), lds, s, a);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.splits == 1)
         return e;
@@ -531,7 +804,8 @@ hipError_t launch_kv_attention(const KvAttnArgs &a, hipStream_t s)
     case 64: return go_attn<64>(a, s);
     case 128:
         if (a.G == 128)
-            return go_attn_mfma(a, s);
+            // a launch holds fewer than 2^32 threads
+            return a.nq < (1 << 23) ? go_attn_mfma<8>(a, s) : go_attn_mfma<4>(a, s);
         return go_attn<128>(a, s);
     case 256: return go_attn<256>(a, s);
     }
