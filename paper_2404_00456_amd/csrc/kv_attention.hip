@@ -323,7 +323,7 @@ __device__ __forceinline__ uint32_t split_h(float w)
 {
     const _Float16 hi = (_Float16)w;
     const float f = (float)hi;
-    const _Float16 lo = (_Float16)(f < __builtin_inff() ? w - f : f);
+    const _Float16 lo = (_Float16)(__builtin_fabsf(f) < __builtin_inff() ? w - f : f);
     return (uint32_t)__builtin_bit_cast(uint16_t, hi) |
            ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
 }

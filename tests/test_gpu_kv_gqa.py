@@ -86,6 +86,21 @@ def test_tokens_of_infinite_negative_score(dev, rep):
     assert np.all(d <= 2.0 ** -10 * np.abs(part.astype(np.float64)) + 2.0 ** -16 * 9.0)
 
 
+@pytest.mark.parametrize("rep", [1, 8])
+@pytest.mark.parametrize("inf", [np.inf, -np.inf])
+def test_infinite_value_scale(dev, rep, inf):
+    """An infinite scale of a value row whose codes are all positive: the
+    output is that infinity, not the NaN of its parts' difference."""
+    import paper_2404_00456_amd as qq
+    rng = np.random.default_rng(70 + rep)
+    k, v = rand_cache(rng, 2, 40, 128, 128), rand_cache(rng, 2, 40, 128, 128)
+    v[0][:, 0], v[1][:, 0] = 0x31, inf
+    q = (rng.standard_normal((2 * rep, 128)) * 0.1).astype(np.float16)
+    out = H(qq.quarot_kv_decode_attention(T(q, dev), tuple(T(x, dev) for x in k),
+                                          tuple(T(x, dev) for x in v), 40))
+    assert np.all(out == inf)
+
+
 def test_more_rows_than_a_wide_launch_holds(dev, orc):
     """2^23 rows of one token: out is the dequantized value row."""
     import torch
