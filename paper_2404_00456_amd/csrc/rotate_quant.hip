@@ -284,12 +284,13 @@ __device__ __forceinline__ float silu_f32(float g)
     // [1, 2^127); where 1 / d would be subnormal the quotient is far below
     // fp16 and only its sign counts, which is g's).  For every finite fp16 gate
     // this is the IEEE quotient's encoding down to 2^-110 and a zero or that
-    // quotient below.
+    // quotient below.  The fixup sets the sign and gives an infinite gate its
+    // infinity, which the correction alone would turn into NaN.
     const float d = 1.0f + e;
     float r0 = __builtin_amdgcn_rcpf(d);
     r0 = __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);
     const float q0 = g * r0;
-    return __builtin_copysignf(__builtin_fmaf(__builtin_fmaf(-d, q0, g), r0, q0), g);
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, q0, g), r0, q0), d, g);
 }
 
 // The down-projection input h = RN16(RN(silu(g) u)), as binary32.

@@ -86,3 +86,16 @@ def test_largem_swiglu_edge_rows(dev, orc, n):
     q6, s6 = q.quarot_swiglu_quant_e3m2(T(gate, dev), T(up, dev), clip_ratio=0.9)
     assert_same(H(q6), H(q.quarot_pack_e3m2(codes)), f"swiglu e3m2 codes n={n}")
     assert_same(H(s6).view(np.uint16), rs.view(np.uint16), f"swiglu e3m2 scales n={n}")
+
+
+def test_swiglu_infinite_gate(dev):
+    """silu(+inf) = inf and silu(-inf) = -inf / (1 + e^88) = -inf in the
+    binary32 recipe; NaN stays NaN."""
+    import paper_2404_00456_amd as q
+    g = np.array([np.inf, -np.inf, np.nan, np.inf, -np.inf, 3.0, 0.0, -0.0], np.float16)
+    u = np.array([2.0, 2.0, 2.0, -2.0, -2.0, np.inf, 1.0, 1.0], np.float16)
+    got = H(q.quarot_swiglu(T(g, dev), T(u, dev)))
+    ref = np.array([np.inf, -np.inf, np.nan, -np.inf, np.inf, np.inf, 0.0, -0.0], np.float16)
+    assert np.isnan(got[2])
+    assert_same(got[[0, 1, 3, 4, 5, 6, 7]].view(np.uint16),
+                ref[[0, 1, 3, 4, 5, 6, 7]].view(np.uint16), "infinite gates")
