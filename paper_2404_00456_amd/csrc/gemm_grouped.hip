@@ -1023,11 +1023,214 @@ __global__ __launch_bounds__(THREADS, 1) void k_gemm_w4a4_grouped_e3m2(GemmArgs 
 }  // namespace
 
 namespace {
+// ------------------------------------------------------------------------
+// Few X rows (decoding steps, short prompts): as in the per-token kernels for
+// few rows, W goes straight from memory to registers and K is split between a
+// block's waves, so that N / 16 blocks of eight waves read it with everything
+// in flight, where one 256 x 128 tile per block leaves 224 of 256 CUs idle on
+// 4096 outputs.  The definition adds the groups in order, so the waves leave
+// each group's integers in LDS and every thread then sums its own outputs over
+// the groups, RN(RN(f32(acc_g) sx) sw) one after the other, from there.
+//
+// A pass covers P = 8 U groups, U consecutive ones per wave; the next pass's
+// loads are issued before this pass's products.
+//
+// Groups of 128, against the kernels above: 1 x 4096 (K = 4096) 73.4 -> 4.3 us,
+// 16 x 11008 54.4 -> 10.4, 64 x 5120 (K = 13824) 175 -> 67, 256 x 4096 (K = 4096)
+// 57.4 -> 39.4.  With one row tile the bound is the read of W and the start-up;
+// with more, the sums over the groups (three LDS reads per output and group,
+// in order) and the blocks' reads of X from the L2.
+template <int GS, int MT>
+struct GroupFew {
+    static constexpr int WV = 8;
+    static constexpr int U = (MT < 4 ? 4 : 2) * 128 / (GS < 128 ? 128 : GS);  // groups per wave
+    static constexpr int P = WV * U;                 // groups per pass
+    static constexpr int PITCH = 20;                 // dwords per m of a 16 x 16 tile
+    static constexpr int CELLS = MT * 16 * PITCH;    // dwords per group
+    static constexpr int SC = 16 * MT + 16;          // scales per group: sx, then sw
+    static constexpr int LDS = P * (CELLS + SC) * 4;
+    static constexpr int OUT = (MT * 256 + 511) / 512;  // outputs per thread
+    static constexpr int SUB = GS / 64;              // MFMA substeps per group
+};
+
+template <int GS, int MT>
+__global__ __launch_bounds__(512) void k_gemm_grouped_few(GemmArgs a)
+{
+    typedef GroupFew<GS, MT> C;
+    extern __shared__ __align__(16) uint32_t few[];  // [P][CELLS], then [P][SC] floats
+    float *scl = reinterpret_cast<float *>(few + C::P * C::CELLS);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+    const int M = a.M, N = a.N, NG = a.K / GS;
+    const int64_t pitch = a.K / 2;
+    // consecutive tiles, m fastest, on one XCD (block b runs on XCD b % 8)
+    const int TM = (M + 16 * MT - 1) / (16 * MT);
+    const int nblk = gridDim.x, b = blockIdx.x, x = b & 7;
+    const int t = x * (nblk >> 3) + min(x, nblk & 7) + (b >> 3);
+    const int m0 = (t % TM) * 16 * MT, n0 = (t / TM) * 16;
+
+    // rows past the edge read the last row instead
+    const uint8_t *wrow = a.wq + min(n0 + r16, N - 1) * pitch;
+    const uint8_t *xrow[MT];
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
+        xrow[j] = a.xq + min(m0 + 16 * j + r16, M - 1) * pitch;
+
+    struct Slice {
+        uint2 d[C::SUB];
+    };
+    // A group of a row: 8 bytes per substep, W and X alike, so that the order
+    // of k inside the group does not matter.
+    auto load = [&](const uint8_t *row, int grp) {
+        Slice s;
+        const uint8_t *p = row + (int64_t)grp * (GS / 2);
+        if constexpr (GS == 64) {
+            s.d[0] = *reinterpret_cast<const uint2 *>(p + 8 * g);
+        } else {
+#pragma unroll
+            for (int h = 0; h < GS / 128; ++h) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(p + 64 * h + 16 * g);
+                s.d[2 * h] = make_uint2(v.x, v.y);
+                s.d[2 * h + 1] = make_uint2(v.z, v.w);
+            }
+        }
+        return s;
+    };
+    Slice ws[2][C::U], xs[2][C::U][MT];
+    auto load_pass = [&](int buf, int base) {
+#pragma unroll
+        for (int u = 0; u < C::U; ++u) {
+            const int grp = min(base + wave * C::U + u, NG - 1);  // past the last: not summed
+            ws[buf][u] = load(wrow, grp);
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+                xs[buf][u][j] = load(xrow[j], grp);
+        }
+    };
+    const int n = tid & 15, lm = tid >> 4;  // this thread's outputs: column n, rows lm + 32 i
+    float y[C::OUT];
+#pragma unroll
+    for (int i = 0; i < C::OUT; ++i)
+        y[i] = 0.0f;
+
+    auto pass = [&](int buf, int base) {
+        const int here = min(C::P, NG - base);
+        for (int i = tid; i < here * C::SC; i += 512) {
+            const int grp = base + i / C::SC, c = i % C::SC;
+            scl[i] = h2f(c < 16 * MT ? a.sx[(int64_t)grp * M + min(m0 + c, M - 1)]
+                                     : a.sw[(int64_t)grp * N + min(n0 + c - 16 * MT, N - 1)]);
+        }
+#pragma unroll
+        for (int u = 0; u < C::U; ++u) {
+            v4i acc[MT];
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+                acc[j] = v4i{0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < C::SUB; ++s) {
+                const v4i w = widen(ws[buf][u].d[s]);
+#pragma unroll
+                for (int j = 0; j < MT; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, widen(xs[buf][u][j].d[s]),
+                                                                   acc[j], 0, 0, 0);
+            }
+            // lane holds n = 4 g + r (r = 0..3) of m = r16, as 256 acc_g
+#pragma unroll
+            for (int j = 0; j < MT; ++j)
+                *reinterpret_cast<uint4 *>(few + (wave * C::U + u) * C::CELLS +
+                                           (16 * j + r16) * C::PITCH + 4 * g) =
+                    __builtin_bit_cast(uint4, acc[j]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < C::OUT; ++i) {
+            const int m = lm + 32 * i;
+            if (m < 16 * MT) {
+#pragma unroll 8
+                for (int k = 0; k < here; ++k) {
+                    const int iv = (int)few[k * C::CELLS + m * C::PITCH + n] >> 8;
+                    const float tt = (float)iv * scl[k * C::SC + m];
+                    y[i] += tt * scl[k * C::SC + 16 * MT + n];
+                }
+            }
+        }
+    };
+
+    load_pass(0, 0);
+    for (int base = 0; base < NG; base += 2 * C::P) {
+        if (base + C::P < NG)
+            load_pass(1, base + C::P);
+        __builtin_amdgcn_sched_barrier(0);
+        pass(0, base);
+        if (base + C::P >= NG)
+            break;
+        __syncthreads();  // the next pass overwrites what was read
+        if (base + 2 * C::P < NG)
+            load_pass(0, base + 2 * C::P);
+        __builtin_amdgcn_sched_barrier(0);
+        pass(1, base + C::P);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < C::OUT; ++i) {
+        const int m = lm + 32 * i;
+        if (m < 16 * MT && m0 + m < M && n0 + n < N)
+            a.y[(int64_t)(m0 + m) * N + n0 + n] = f2h(y[i]);
+    }
+}
+
+template <int GS, int MT>
+hipError_t go_few(const GemmArgs &a, hipStream_t s)
+{
+    constexpr int lds = GroupFew<GS, MT>::LDS;
+    const void *fn = (const void *)k_gemm_grouped_few<GS, MT>;
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess)
+            return e;
+    }
+    const int64_t blocks = (int64_t)((a.M + 16 * MT - 1) / (16 * MT)) * ((a.N + 15) / 16);
+    hipLaunchKernelGGL((k_gemm_grouped_few<GS, MT>), dim3((unsigned)blocks), dim3(512), lds, s, a);
+    return hipGetLastError();
+}
+
+// Row tiles (16 rows each) per block of the kernel for few rows, or 0 where the
+// 256 x 128 tiles are the better.  Those take about the same time per round of
+// the CUs whatever part of a tile is there (K = 4096, GS 64, 128, 256: 83, 55,
+// 59 us); a block of the few-row kernel takes, per block a CU gets, 6, 4, 3.3 us
+// with 1 row tile, 14.5, 7, 5.7 with 2 and 25, 11, 7 with 4, and both grow alike
+// with K.  The lines lie some 20% before the crossing (K = 4096, GS 128:
+// 256 x 4096, 4 blocks per CU: 39 against 57 us; 384 x 4096, 6: 58 against 58;
+// 128 x 11008, 5.4: 58 against 56).  Rows past 512 were not measured.
+template <int GS>
+int few_tiles(const GemmArgs &a, int cus)
+{
+    if (a.M > 512)
+        return 0;
+    const int i = a.M <= 16 ? 0 : a.M <= 32 ? 1 : 2, rows = 16 << i;
+    static constexpr int most[3][3] = {{10, 4, 3}, {10, 6, 4}, {12, 8, 8}};  // blocks per CU
+    const int64_t blocks = (int64_t)((a.M + rows - 1) / rows) * ((a.N + 15) / 16);
+    const int64_t tiles = (int64_t)((a.M + BM - 1) / BM) * ((a.N + GBN - 1) / GBN);
+    const int64_t rounds = (tiles + cus - 1) / cus;
+    return blocks <= rounds * cus * most[GS / 128][i] ? 1 << i : 0;
+}
+
 template <int GS>
 hipError_t gemm_grouped_as(const GemmArgs &a, hipStream_t s)
 {
     if (a.K % GroupTile<GS>::KS)
         return hipErrorInvalidValue;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        cus = 256;
+    switch (few_tiles<GS>(a, cus)) {
+    case 1: return go_few<GS, 1>(a, s);
+    case 2: return go_few<GS, 2>(a, s);
+    case 4: return go_few<GS, 4>(a, s);
+    }
     const int TM = (a.M + BM - 1) / BM, TN = (a.N + GBN - 1) / GBN;
     const int tiles = TM * TN;
     if (a.M % 8 == 0 && a.N % 8 == 0) {
@@ -1038,11 +1241,6 @@ hipError_t gemm_grouped_as(const GemmArgs &a, hipStream_t s)
                                            hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
         if (e != hipSuccess)
             return e;
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            cus = 256;
         int grid = (tiles < cus || a.K / C::KS < C::RS) ? tiles : cus;
         if (grid >= 8 && tiles % 8 == 0)
             grid -= grid % 8;

@@ -67,6 +67,22 @@ def test_gemm_grouped(dev, orc, M, N, K, group):
     assert_fp16_close(H(y), ry, f"grouped y M={M} N={N} K={K} G={group}")
 
 
+# few rows (k_gemm_grouped_few): 1, 2 and 4 row tiles with their edges, ragged
+# N, and groups on both sides of one and of two passes (8 to 32 groups each)
+@pytest.mark.parametrize("M", [1, 15, 16, 17, 32, 33, 63, 64])
+@pytest.mark.parametrize("N,groups", [(8, 2), (17, 8), (40, 9), (15, 16), (136, 17), (31, 32),
+                                      (64, 33), (9, 64), (33, 66)])
+@pytest.mark.parametrize("group", [64, 128, 256])
+def test_gemm_grouped_few_rows(dev, orc, M, N, groups, group):
+    import paper_2404_00456_amd as q
+    K = groups * group // 128 * 128
+    xq, sx, wq, sw = rand_group_case(M * 7 + N + groups, M, N, K, group)
+    y = q.quarot_w4a4_gemm_grouped(T(xq, dev), T(sx, dev), T(wq, dev), T(sw, dev), group=group)
+    ry = orc.gemm_grouped(xq, sx, wq, sw, group=group)
+    assert_same(H(y).view(np.uint16), ry.view(np.uint16),
+                f"grouped few rows M={M} N={N} K={K} G={group}")
+
+
 @pytest.mark.parametrize("M,N,K,group", [(2200, 8400, 1024, 128), (2048, 8448, 512, 64),
                                          (2304, 8448, 768, 256)])
 def test_gemm_grouped_many_tiles(dev, orc, M, N, K, group):
