@@ -1253,6 +1253,23 @@ __device__ __forceinline__ void f16_split(v2h t, v2h &h, v2h &l)
     l = (s - h) * v2h{(_Float16)1024.0f, (_Float16)1024.0f};
 }
 
+// Any two fp16 inputs (raw bits) as t 2^7 = w 2^15 + h + l 2^-10, all fp16 and
+// exact: w = rint(t / 256) and the rest, at most 128, as above.  An exponent of
+// all ones, which a product silu(g) u past the largest fp16 leaves in h, counts
+// as the next binade, as in f16_planes: one step of the exponent, e, goes from
+// t to the factors.
+__device__ __forceinline__ void f16_split_wide(uint32_t bits, v2h &w, v2h &h, v2h &l)
+{
+    auto h2 = [](uint32_t u) { return __builtin_bit_cast(v2h, u); };
+    const uint32_t e = (((bits & 0x7C007C00u) + 0x04000400u) >> 5) & 0x04000400u;
+    const v2h x = h2(bits ^ e);
+    w = rint2(x * h2(0x1C001C00u + e));  // 2^-8, or 2^-7
+    const v2h s = __builtin_elementwise_fma(w, h2(0xDC00DC00u - e), x) *  // -256, or -128
+                  h2(0x58005800u + e);                                    // 128, or 256
+    h = rint2(s);
+    l = (s - h) * v2h{(_Float16)1024.0f, (_Float16)1024.0f};
+}
+
 template <int M, int RT, int EPI>
 struct LargemLds {
     static constexpr int PLANE = RT * HmF16A<M>::KB * 1024;
@@ -1271,7 +1288,8 @@ struct LargemLds {
 // below 172 * 512, so v_mfma_f32_16x16x32_f16 accumulates both exactly in any
 // order, and fma(sum l, 2^-10, sum h) is 2^7 u with the one rounding the
 // definition asks for.  The factor 2^-7 joins c, exactly.  (A row with larger
-// values takes a third operand and binary64 at the end, see below.)
+// values takes a third operand and binary64 at the end, see below: 2048 x 11008,
+// SwiGLU, all rows such: 100 us, 91 without the step of the exponent.)
 //
 // The four waves split the row into operands, 32 inputs of 16 groups at a
 // time, through LDS; each then multiplies all groups by the column tiles
@@ -1425,24 +1443,24 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem_f16(RotArgs a)
             }
         } else {
             // A value of 512 or more somewhere in the row: the plane holds t
-            // itself; t = h1 + t1 with h1 = rint(t) (exact in fp16) and
-            // |t1| <= 1/2 split as above.  The three exact sums meet in
-            // binary64 (multiples of 2^-17 below 2^31).
+            // itself, split by f16_split_wide.  The three exact sums meet in
+            // binary64 (multiples of 2^-17 below 2^32).
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
-                v4f s1[CTW], sh[CTW], sl[CTW];
+                v4f sw[CTW], sh[CTW], sl[CTW];
 #pragma unroll
                 for (int i = 0; i < CTW; ++i)
-                    s1[i] = sh[i] = sl[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+                    sw[i] = sh[i] = sl[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 1
                 for (int kb = 0; kb < KB; ++kb) {
-                    const v8h tv = plane(0, rt, kb);
-                    const v8h h1 = __builtin_elementwise_rint(tv);
-                    v8h hv, lv;
+                    const uint4 tv = __builtin_bit_cast(uint4, plane(0, rt, kb));
+                    const uint32_t tw[4] = {tv.x, tv.y, tv.z, tv.w};
+                    v8h wv, hv, lv;
 #pragma unroll
                     for (int p = 0; p < 4; ++p) {
-                        v2h h, l;
-                        f16_split(v2h{tv[2 * p] - h1[2 * p], tv[2 * p + 1] - h1[2 * p + 1]}, h, l);
+                        v2h w, h, l;
+                        f16_split_wide(tw[p], w, h, l);
+                        wv[2 * p] = w[0], wv[2 * p + 1] = w[1];
                         hv[2 * p] = h[0], hv[2 * p + 1] = h[1];
                         lv[2 * p] = l[0], lv[2 * p + 1] = l[1];
                     }
@@ -1451,7 +1469,7 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem_f16(RotArgs a)
                         // (from the table: H is indexed at compile time)
                         const v8h Hk = __builtin_bit_cast(
                             v8h, hsrc[(min(wave + W * i, CT - 1) * KB + kb) * 64]);
-                        s1[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, h1, s1[i], 0, 0, 0);
+                        sw[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, wv, sw[i], 0, 0, 0);
                         sh[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, hv, sh[i], 0, 0, 0);
                         sl[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, lv, sl[i], 0, 0, 0);
                     }
@@ -1462,7 +1480,7 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem_f16(RotArgs a)
                     for (int r = 0; r < 4; ++r)
                         v[i][rt][r] = (float)__builtin_fma(
                             (double)sl[i][r], 0x1p-10,
-                            __builtin_fma((double)s1[i][r], 128.0, (double)sh[i][r]));
+                            __builtin_fma((double)sw[i][r], 32768.0, (double)sh[i][r]));
             }
         }
 

@@ -99,3 +99,39 @@ def test_swiglu_infinite_gate(dev):
     assert np.isnan(got[2])
     assert_same(got[[0, 1, 3, 4, 5, 6, 7]].view(np.uint16),
                 ref[[0, 1, 3, 4, 5, 6, 7]].view(np.uint16), "infinite gates")
+
+
+@pytest.mark.parametrize("n", [1728, 3456, 6912, 13824, 2752, 5504, 11008])
+def test_largem_past_the_largest_fp16(dev, orc, n):
+    """A product silu(g) u past the largest fp16 is an infinity in h.  The
+    rotation reads an exponent of all ones as the next binade (infinity as
+    65536), so that such a row keeps its codes: those of half the row, with
+    twice its scale."""
+    import paper_2404_00456_amd as q
+    say(f"largem past fp16 n={n}")
+    rng = np.random.default_rng(n)
+    half = (rng.standard_normal((6, n)) * 40).astype(np.float16)
+    half[np.abs(half) < 1] = 1  # exact when halved or doubled
+    half[0, 5] = half[1, n - 1] = 32768
+    signs = rng.choice(np.array([-1, 1], np.float16), n)
+    half[1, ::301] = 32768 * signs[::301]
+    half[2] = 32768 * signs
+    half[3, ::7] = (32768 + 32 * 777) * signs[::7]  # a NaN's significand, doubled
+    half[4, ::11] = 32752 * signs[::11]  # the largest fp16, doubled
+    with np.errstate(over="ignore"):
+        x = half * np.float16(2)
+    top = np.abs(half) >= 32768  # the exponent's last step, same significand
+    x[top] = (half[top].view(np.uint16) + 0x0400).view(np.float16)
+    rq, rs = orc.quant_int4(half, rotate=True, clip=0.9)
+    twice = (rs.astype(np.float32) * 2).astype(np.float16).view(np.uint16)
+    codes, scale = q.quarot_quant_int4(T(x, dev), clip_ratio=0.9)
+    assert_same(H(codes), rq, f"codes n={n}")
+    assert_same(H(scale).view(np.uint16), twice, f"scales n={n}")
+    # silu(64) = 64 in binary32, so h = 64 u, infinite from |u| = 1024 on
+    up = half[[0, 1, 2, 4, 5]] / np.float16(32)
+    rq, rs = orc.swiglu_quant_int4(np.full_like(up, 32), up, rotate=True, clip=0.9)
+    twice = (rs.astype(np.float32) * 2).astype(np.float16).view(np.uint16)
+    codes, scale = q.quarot_swiglu_quant_int4(T(np.full_like(up, 64), dev), T(up, dev),
+                                              clip_ratio=0.9)
+    assert_same(H(codes), rq, f"swiglu codes n={n}")
+    assert_same(H(scale).view(np.uint16), twice, f"swiglu scales n={n}")
