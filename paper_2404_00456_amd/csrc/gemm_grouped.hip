@@ -1195,27 +1195,6 @@ hipError_t go_few(const GemmArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// Row tiles (16 rows each) per block of the kernel for few rows, or 0 where the
-// 256 x 128 tiles are the better.  Those take about the same time per round of
-// the CUs whatever part of a tile is there (K = 4096, GS 64, 128, 256: 83, 55,
-// 59 us); a block of the few-row kernel takes, per block a CU gets, 6, 4, 3.3 us
-// with 1 row tile, 14.5, 7, 5.7 with 2 and 25, 11, 7 with 4, and both grow alike
-// with K.  The lines lie some 20% before the crossing (K = 4096, GS 128:
-// 256 x 4096, 4 blocks per CU: 39 against 57 us; 384 x 4096, 6: 58 against 58;
-// 128 x 11008, 5.4: 58 against 56).  Rows past 512 were not measured.
-template <int GS>
-int few_tiles(const GemmArgs &a, int cus)
-{
-    if (a.M > 512)
-        return 0;
-    const int i = a.M <= 16 ? 0 : a.M <= 32 ? 1 : 2, rows = 16 << i;
-    static constexpr int most[3][3] = {{10, 4, 3}, {10, 6, 4}, {12, 8, 8}};  // blocks per CU
-    const int64_t blocks = (int64_t)((a.M + rows - 1) / rows) * ((a.N + 15) / 16);
-    const int64_t tiles = (int64_t)((a.M + BM - 1) / BM) * ((a.N + GBN - 1) / GBN);
-    const int64_t rounds = (tiles + cus - 1) / cus;
-    return blocks <= rounds * cus * most[GS / 128][i] ? 1 << i : 0;
-}
-
 template <int GS>
 hipError_t gemm_grouped_as(const GemmArgs &a, hipStream_t s)
 {
@@ -1226,7 +1205,7 @@ hipError_t gemm_grouped_as(const GemmArgs &a, hipStream_t s)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         cus = 256;
-    switch (few_tiles<GS>(a, cus)) {
+    switch (few_tiles(a.M, a.N, GS, cus)) {
     case 1: return go_few<GS, 1>(a, s);
     case 2: return go_few<GS, 2>(a, s);
     case 4: return go_few<GS, 4>(a, s);

@@ -57,6 +57,9 @@ inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int cus, in
             (int)grid};
 }
 
+// Blocks of 512 threads that one launch can hold: fewer than 2^32 threads.
+constexpr int64_t MOST_BLOCKS = (int64_t(1) << 23) - 1;
+
 // The path of a product: the tiled plan above, or the kernels for fewer rows
 // or outputs than fill it.
 enum class GemmPath {
@@ -94,7 +97,6 @@ inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, in
     if (bits == 4 && K % 128 != 0)
         return {GemmPath::Tiled, 0, 0, 0};
     auto up = [](int64_t x, int64_t d) { return (x + d - 1) / d; };
-    constexpr int64_t MOST = 0x7FFFFFFF;  // blocks of a grid
     const int64_t ks = bits == 8 ? K / 64 : K / 128;
     const int f = bits == 6 ? 0 : bits == 4 ? 1 : 2;
 
@@ -125,7 +127,7 @@ inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, in
     const int64_t lo = bits == 6 ? 145 : 190, hi = bits == 6 ? 175 : 210;  // 1/100 ns
     const int64_t cu = lo * units, l2 = hi * blocks * (16 * nt + rows) / cus;
     const int64_t stream = 2000 + ks * (cu > l2 ? cu : l2) / 100;
-    if (stream < best && blocks <= MOST) {
+    if (stream < best && blocks <= MOST_BLOCKS) {
         best = stream;
         plan = {GemmPath::Stream, mt, nt, (int)blocks};
     }
@@ -141,12 +143,33 @@ inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, in
         // 3% on the safe side
         const int64_t t = (2500 + r * (ks * m.step[f] * (r > 1 ? m.more : 100) / 100 + 1000)) *
                           103 / 100;
-        if (t < best && n <= MOST) {
+        if (t < best && n <= MOST_BLOCKS) {
             best = t;
             plan = {GemmPath::Mid, m.a, m.b, (int)n};
         }
     }
     return plan;
+}
+
+// Group-wise products: row tiles (16 rows each) per block of the kernel for few
+// rows, or 0 where the 256 x 128 tiles are the better.  Those take about the
+// same time per round of the CUs whatever part of a tile is there (K = 4096,
+// groups of 64, 128, 256: 83, 55, 59 us); a block of the few-row kernel takes,
+// per block a CU gets, 6, 4, 3.3 us with 1 row tile, 14.5, 7, 5.7 with 2 and 25,
+// 11, 7 with 4, and both grow alike with K.  The lines lie some 20% before the
+// crossing (K = 4096, groups of 128: 256 x 4096, 4 blocks per CU: 39 against 57
+// us; 384 x 4096, 6: 58 against 58; 128 x 11008, 5.4: 58 against 56).  Rows past
+// 512 were not measured.
+inline int few_tiles(int64_t M, int64_t N, int group, int cus)
+{
+    if (M > 512)
+        return 0;
+    const int i = M <= 16 ? 0 : M <= 32 ? 1 : 2, rows = 16 << i;
+    static constexpr int most[3][3] = {{10, 4, 3}, {10, 6, 4}, {12, 8, 8}};  // blocks per CU
+    const int64_t blocks = (M + rows - 1) / rows * ((N + 15) / 16);
+    const int64_t tiles = (M + 255) / 256 * ((N + 127) / 128);
+    const int64_t rounds = (tiles + cus - 1) / cus;
+    return blocks <= MOST_BLOCKS && blocks <= rounds * cus * most[group / 128][i] ? 1 << i : 0;
 }
 
 }  // namespace gemm

@@ -8,6 +8,7 @@
 
 #include "gemm_plan.hpp"
 
+using quarot::gemm::few_tiles;
 using quarot::gemm::GemmPath;
 using quarot::gemm::plan_path;
 
@@ -15,7 +16,8 @@ int main()
 {
     const long long Ms[] = {1,  15,  16,  17,  32,   33,    64,      65,
                             90, 128, 333, 517, 1024, 16384, 1 << 20, 1 << 30};
-    const long long Ns[] = {1, 16, 17, 250, 1376, 4096, 8190, 11008, 28672, 1 << 20};
+    const long long Ns[] = {1,    16,    17,    250,     1376,    4096,   8190,
+                            11008, 28672, 1 << 20, 1 << 27, 1 << 29, 1 << 30};
     const long long Ks[] = {64, 128, 192, 256, 4096, 11008, 28672, 65536};
     int failures = 0, taken[3] = {0, 0, 0};
     for (long long M : Ms)
@@ -45,12 +47,29 @@ int main()
                             un = 64 * p.b;
                         }
                         const long long want = (M + um - 1) / um * ((N + un - 1) / un);
-                        if (!ok || p.grid != want || (bits == 4 && K % 128)) {
+                        // blocks of 512 threads, fewer than 2^32 threads in a launch
+                        if (!ok || p.grid != want || want >= 1 << 23 ||
+                            (bits == 4 && K % 128)) {
                             std::printf("FAIL M=%lld N=%lld K=%lld bits=%d: path %d %d %d grid %d\n",
                                         M, N, K, bits, (int)p.path, p.a, p.b, p.grid);
                             ++failures;
                         }
                     }
+    // group-wise products: the same bound
+    for (long long M : Ms)
+        for (long long N : Ns)
+            for (int group : {64, 128, 256})
+                for (int cus : {64, 256, 304}) {
+                    const int tiles = few_tiles(M, N, group, cus);
+                    const long long rows = 16 * tiles;
+                    if (tiles != 0 &&
+                        ((tiles != 1 && tiles != 2 && tiles != 4) || M > 512 ||
+                         (M + rows - 1) / rows * ((N + 15) / 16) >= 1 << 23)) {
+                        std::printf("FAIL group-wise M=%lld N=%lld group=%d: %d\n", M, N, group,
+                                    tiles);
+                        ++failures;
+                    }
+                }
     for (int n : taken)
         if (!n) {
             std::printf("FAIL a path is never taken\n");
