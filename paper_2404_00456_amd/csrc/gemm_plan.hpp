@@ -74,22 +74,29 @@ struct PathPlan {
 };
 
 // Times are estimated in ns and the smallest wins.  The constants were fitted
-// to 327 measured shapes (e3m2, int4 and int8 codes; M = 1 .. 8000, N = 1024
-// .. 28672, K = 4096 .. 28672, 256 CUs): the choice took 0.3% more time than
-// the best kernel of each shape on average, and none of them lost more than 2%
-// against the tiled kernels.  A kernel's time is a start-up plus rounds of
-// its blocks over the CUs times k-steps times what one step of a tile takes:
+// to measured shapes of e3m2, int4 and int8 codes on 256 CUs: 327 of serving
+// programs (K = 4096 .. 28672), then, for what a round of blocks costs beside
+// its k-steps, 4653 random ones (M = 1 .. 30000, N = 16 .. 32768, K = 64 ..
+// 30720).  Over the latter the choice takes 2.9% more time than the fastest of
+// all tiles on average, 6 shapes lose more than 4% against the tiled kernels
+// and the worst 14%; without the costs per round 65 lost more than 4% and the
+// worst took 2.8 times the time (11964 x 1612, K = 128 on int4: stream 68 us,
+// tiled 24, mid 18).  A kernel's time is a start-up plus rounds of its blocks
+// over the CUs times k-steps times what one step of a tile takes:
 //  * Stream: a block's time per k-step goes with its 16 b columns plus its
 //    rows, at a rate set by the CU (LO) or, with every CU busy, by the L2s
 //    (HI).  Of its widths b, rounds * (16 b + rows) picks the fastest (within
 //    9% in 120 shapes): wide where N gives every CU a block all the same
 //    (61 x 28672, K = 8192: 1, 2, 4 take 68, 52, 40 us), narrow where it does not
-//    (61 x 4096, K = 4096: 5.3, 6.2, 7.9 us).
+//    (61 x 4096, K = 4096: 5.3, 6.2, 7.9 us).  With few k-steps a block's
+//    start and end are what takes time, 1.1 us and 0.9 per 1000 outputs.
 //  * Mid: STEP, a fifth more for the small tiles when they come in several
-//    rounds (their operand traffic then meets the L2s' limit).
+//    rounds (their operand traffic then meets the L2s' limit), 1 us per round
+//    and 0.06 per 1000 outputs of a tile for each round but the last.
 //  * Tiled: the 128-row tiles take 530 to 1250 ns per k-step, the 256-row
 //    tiles 850 to 1500 (600 when half of them is padding); the split-k kernel
 //    starts up in 11 us and waits for HBM when W exceeds the last-level cache.
+//    2 and 4 us for the stores of each round but the last.
 // For instance 333 x 11008, K = 4096 on e3m2: stream 33 us, mid 128 x 192
 // 18.7, tiled 28.4; 2048 x 4096, K = 11008: mid 58.4, tiled 55.5.
 inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, int stages)
@@ -102,14 +109,15 @@ inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, in
 
     const GemmPlan g = plan_gemm(M, N, K, bits, cus, stages);
     const bool big = g.kernel == GemmKernel::Tile256;
-    const int64_t rounds = up(up(M, big ? 256 : 128) * up(N, 256), g.grid);
+    const int64_t rounds = up(up(M, big ? 256 : 128) * up(N, 256), g.grid < cus ? g.grid : cus);
     int64_t step;
     if (big)
         step = M > 128 ? (bits == 6 ? 980 : bits == 4 ? 1500 : 850)
                        : (bits == 6 ? 600 : bits == 4 ? 1250 : 610);
     else
         step = bits == 6 ? (N * K > 100000000 ? 660 : 530) : bits == 4 ? 1250 : 610;
-    int64_t best = (g.kernel == GemmKernel::Ksplit ? 11000 : 8000) + rounds * ks * step;
+    int64_t best = (g.kernel == GemmKernel::Ksplit ? 11000 : 8000) + rounds * ks * step +
+                   (rounds - 1) * (big ? 4000 : 2000);
     PathPlan plan = {GemmPath::Tiled, 0, 0, 0};
 
     const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
@@ -126,7 +134,9 @@ inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, in
     }
     const int64_t lo = bits == 6 ? 145 : 190, hi = bits == 6 ? 175 : 210;  // 1/100 ns
     const int64_t cu = lo * units, l2 = hi * blocks * (16 * nt + rows) / cus;
-    const int64_t stream = 2000 + ks * (cu > l2 ? cu : l2) / 100;
+    const int64_t steps = ks * (cu > l2 ? cu : l2) / 100;
+    const int64_t ends = blocks > cus ? blocks * (1100 + 14 * nt * rows) / cus : 0;
+    const int64_t stream = 2000 + (steps > ends ? steps : ends);
     if (stream < best && blocks <= MOST_BLOCKS) {
         best = stream;
         plan = {GemmPath::Stream, mt, nt, (int)blocks};
@@ -141,7 +151,8 @@ inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, in
     for (const auto &m : mids) {
         const int64_t n = up(M, 32 * m.a) * up(N, 64 * m.b), r = up(n, cus);
         // 3% on the safe side
-        const int64_t t = (2500 + r * (ks * m.step[f] * (r > 1 ? m.more : 100) / 100 + 1000)) *
+        const int64_t t = (2500 + r * (ks * m.step[f] * (r > 1 ? m.more : 100) / 100 + 1000) +
+                           (r - 1) * (50 + 120 * m.a * m.b)) *
                           103 / 100;
         if (t < best && n <= MOST_BLOCKS) {
             best = t;

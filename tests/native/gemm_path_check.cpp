@@ -90,6 +90,10 @@ int main()
         {16384, 8192, 28672, 6, T, 0, 0}, {1777, 4096, 4096, 4, D, 4, 4},
         {16384, 28672, 8192, 4, T, 0, 0}, {517, 5120, 13824, 8, D, 4, 2},
         {32, 4096, 11008, 8, S, 2, 1},   {3000, 8192, 8192, 8, T, 0, 0},
+        // few k-steps over many rounds of blocks: not the streaming kernel
+        {11964, 1612, 128, 4, D, 8, 3},  {3318, 2788, 128, 6, D, 8, 3},
+        {6515, 1660, 128, 4, D, 8, 3},   {86, 27196, 128, 8, D, 4, 2},
+        {6610, 724, 256, 6, D, 4, 3},    {1, 26690, 128, 6, D, 2, 2},
     };
     for (const auto &c : fitted) {
         const auto p = plan_path(c.M, c.N, c.K, c.bits, 256, 3);
