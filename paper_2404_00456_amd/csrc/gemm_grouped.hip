@@ -1205,7 +1205,7 @@ hipError_t gemm_grouped_as(const GemmArgs &a, hipStream_t s)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         cus = 256;
-    switch (few_tiles(a.M, a.N, GS, cus)) {
+    switch (few_tiles(a.M, a.N, a.K, GS, cus)) {
     case 1: return go_few<GS, 1>(a, s);
     case 2: return go_few<GS, 2>(a, s);
     case 4: return go_few<GS, 4>(a, s);

@@ -163,24 +163,35 @@ inline PathPlan plan_path(int64_t M, int64_t N, int64_t K, int bits, int cus, in
 }
 
 // Group-wise products: row tiles (16 rows each) per block of the kernel for few
-// rows, or 0 where the 256 x 128 tiles are the better.  Those take about the
-// same time per round of the CUs whatever part of a tile is there (K = 4096,
-// groups of 64, 128, 256: 83, 55, 59 us); a block of the few-row kernel takes,
-// per block a CU gets, 6, 4, 3.3 us with 1 row tile, 14.5, 7, 5.7 with 2 and 25,
-// 11, 7 with 4, and both grow alike with K.  The lines lie some 20% before the
-// crossing (K = 4096, groups of 128: 256 x 4096, 4 blocks per CU: 39 against 57
-// us; 384 x 4096, 6: 58 against 58; 128 x 11008, 5.4: 58 against 56).  Rows past
-// 512 were not measured.
-inline int few_tiles(int64_t M, int64_t N, int group, int cus)
+// rows, or 0 where the 256 x 128 tiles are the better.  Both times are straight
+// lines in K: the tiles take 6 us and a rate per channel for each round of the
+// CUs, whatever part of a tile is there (one rate with the ring, M and N
+// multiples of 8, and one without); the few-row kernel a start, and then for
+// each block a CU gets a fixed part and a rate per channel.  Fitted to 1981
+// measured products (M = 1 .. 512, N = 16 .. 40000, K = 128 .. 13824, groups of
+// 64, 128, 256, 256 CUs) with an error of 8% for the tiles and 17% for the few
+// rows, and 6% on the safe side: the choice takes 0.3% more time than the
+// faster of the two, 13 products lose more than 4% against the tiles.  Lines on
+// blocks per CU alone, without K, lost 2.6% and 101 (groups of 256, 32 x 31264,
+// K = 256: few 33 us, tiles 9.5; groups of 128, 256 x 4096, K = 4096: 39 against
+// 57).  Rows past 512 were not measured.
+inline int few_tiles(int64_t M, int64_t N, int64_t K, int group, int cus)
 {
     if (M > 512)
         return 0;
-    const int i = M <= 16 ? 0 : M <= 32 ? 1 : 2, rows = 16 << i;
-    static constexpr int most[3][3] = {{10, 4, 3}, {10, 6, 4}, {12, 8, 8}};  // blocks per CU
-    const int64_t blocks = (M + rows - 1) / rows * ((N + 15) / 16);
+    const int i = M <= 16 ? 0 : M <= 32 ? 1 : 2, g = group / 128, rows = 16 << i;
+    // ns per round and 1/10 ns per channel; ns per block and 1/100 ns per channel
+    static constexpr int tile[3][2] = {{253, 197}, {178, 125}, {224, 133}};
+    static constexpr int start[3] = {5000, 3400, 3000};
+    static constexpr int block[3][3] = {{200, 1700, 1650}, {900, 2900, 2500}, {1000, 2650, 1600}};
+    static constexpr int chan[3][3] = {{107, 303, 517}, {59, 122, 206}, {45, 95, 119}};
     const int64_t tiles = (M + 255) / 256 * ((N + 127) / 128);
     const int64_t rounds = (tiles + cus - 1) / cus;
-    return blocks <= MOST_BLOCKS && blocks <= rounds * cus * most[group / 128][i] ? 1 << i : 0;
+    const int64_t tiled = rounds * (6000 + K * tile[g][M % 8 == 0 && N % 8 == 0] / 10);
+    const int64_t blocks = (M + rows - 1) / rows * ((N + 15) / 16);
+    const int64_t per = 100 * block[g][i] + K * chan[g][i];
+    const int64_t few = start[i] + (blocks > cus ? blocks : cus) * per / (100 * cus);
+    return blocks <= MOST_BLOCKS && few * 106 <= tiled * 100 ? 1 << i : 0;
 }
 
 }  // namespace gemm

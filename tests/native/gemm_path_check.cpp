@@ -58,18 +58,38 @@ int main()
     // group-wise products: the same bound
     for (long long M : Ms)
         for (long long N : Ns)
-            for (int group : {64, 128, 256})
-                for (int cus : {64, 256, 304}) {
-                    const int tiles = few_tiles(M, N, group, cus);
-                    const long long rows = 16 * tiles;
-                    if (tiles != 0 &&
-                        ((tiles != 1 && tiles != 2 && tiles != 4) || M > 512 ||
-                         (M + rows - 1) / rows * ((N + 15) / 16) >= 1 << 23)) {
-                        std::printf("FAIL group-wise M=%lld N=%lld group=%d: %d\n", M, N, group,
-                                    tiles);
-                        ++failures;
+            for (long long K : Ks)
+                for (int group : {64, 128, 256})
+                    for (int cus : {64, 256, 304}) {
+                        const int tiles = few_tiles(M, N, K, group, cus);
+                        const long long rows = 16 * tiles;
+                        if (tiles != 0 &&
+                            ((tiles != 1 && tiles != 2 && tiles != 4) || M > 512 ||
+                             (M + rows - 1) / rows * ((N + 15) / 16) >= 1 << 23)) {
+                            std::printf("FAIL group-wise M=%lld N=%lld K=%lld group=%d: %d\n", M, N,
+                                        K, group, tiles);
+                            ++failures;
+                        }
                     }
-                }
+    const struct {
+        long long M, N, K;
+        int group, tiles;
+    } grouped[] = {
+        {1, 4096, 4096, 128, 1},    {16, 11008, 4096, 128, 1},  {64, 5120, 13824, 128, 4},
+        {256, 4096, 4096, 128, 4},  {384, 4096, 4096, 128, 0},  {512, 4096, 11008, 256, 4},
+        {2048, 11008, 4096, 128, 0}, {30, 4096, 4096, 64, 2},
+        // few groups: the few-row kernel's fixed part per block is what takes time
+        {32, 31264, 256, 256, 0},   {16, 28672, 256, 128, 0},   {464, 4096, 256, 256, 0},
+        {80, 8192, 128, 128, 0},    {32, 11008, 256, 128, 0},
+    };
+    for (const auto &c : grouped) {
+        const int tiles = few_tiles(c.M, c.N, c.K, c.group, 256);
+        if (tiles != c.tiles) {
+            std::printf("FAIL group-wise M=%lld N=%lld K=%lld group=%d: %d, want %d\n", c.M, c.N,
+                        c.K, c.group, tiles, c.tiles);
+            ++failures;
+        }
+    }
     for (int n : taken)
         if (!n) {
             std::printf("FAIL a path is never taken\n");
