@@ -17,9 +17,11 @@
 // second kernel combines them.  Groups must be at least 32 wide, so that a
 // lane's 32 elements share one scale and zero.  Head_dim 128 with one group
 // per row takes the matrix-core kernels further below instead, one for a
-// query row per cache row and one for several, with 8 waves in a block.
+// query row per block and one for the query rows of a cache row, with 4 or 8
+// waves in a block (attn_plan.hpp).
 #include <algorithm>
 
+#include "attn_plan.hpp"
 #include "common.hpp"
 
 namespace quarot {
@@ -333,9 +335,14 @@ constexpr int MFMA_U = 4;  // 16-token groups per wave per iteration
 // NW waves share a row's tokens.  Eight keep enough loads in flight for a row
 // to be read whole by one block: 16 x 32 rows of 2047 tokens (143 MB) take
 // 30.2 us, against 37.6 with four waves and four blocks per row.  Sixteen
-// gained nothing (32.6).  The read is what bounds it then (4.7 TB/s).
+// gained nothing (32.6).  The read is what bounds it then (4.7 TB/s).  Four
+// start and end sooner and leave room for others: 700 rows of 100 tokens 6.0 us
+// against 8.2.  Four waves per SIMD (at most 128 registers): with the 132 that
+// four-wave blocks take on their own, three, a CU has room for three instead of
+// four of them and 1024 rows of 100 tokens take 8.2 us instead of 6.8.
 template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_kv_attn_mfma(KvAttnArgs a)
+__global__ __launch_bounds__(64 * NW)
+    __attribute__((amdgpu_waves_per_eu(4, 4))) void k_kv_attn_mfma(KvAttnArgs a)
 {
     constexpr int D = 128;
     __shared__ float red[NW][D + 2];
@@ -520,7 +527,7 @@ __global__ __launch_bounds__(64 * NW) void k_kv_attn_mfma(KvAttnArgs a)
 // all of the wave's tokens; the running maxima are per query (per lane), and
 // when one grows the accumulators are rescaled by factors fetched across
 // lanes.
-constexpr int GQA_R = 8;  // query rows per block
+constexpr int GQA_R = attn::SHARED_ROWS;  // query rows per block
 constexpr int GQA_U = 2;  // 16-token groups per wave per iteration
 
 template <int NW>
@@ -756,38 +763,30 @@ hipError_t go_attn(const KvAttnArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// How many blocks share a cache row's tokens on the matrix path: at most the
-// workspace's a.splits, and one wave of blocks over the 256 compute units,
-// eight waves in each.  More blocks than that read no faster and the partial
-// results cost a second launch and a pass (16 x 32 rows, 2047 tokens: 30.2 us
-// whole, 33.0 in two, 36.6 in four; 40 rows of 8 queries, 4099 tokens: 35.1
-// whole, 16.7 in four, 14.8 in six, 19.4 in sixteen).  That pass costs as much
-// as reading some 600 tokens, so a row is left whole unless splitting takes
-// off more (32 rows: 600 tokens 5.7 whole, 6.4 split; 800 tokens 7.0, 6.3;
-// 128 rows: 1000 tokens 7.9 whole, 9.0 in two; 1300 tokens 10.1, 9.8).
-int mfma_splits(const KvAttnArgs &a, int64_t blocks)
+template <int NW>
+hipError_t go_attn_rows(const KvAttnArgs &a, bool shared, hipStream_t s)
 {
-    const int64_t f = 256 / blocks;
-    if (f < 2 || (int64_t)a.seq_len * (f - 1) <= 600 * f)
-        return 1;
-    return (int)std::min<int64_t>(a.splits, f);
+    const dim3 grid((unsigned)attn::plan_blocks(shared, a.nq / a.rep, a.rep), (unsigned)a.splits);
+    if (shared) {
+        const int lds = NW * std::min(GQA_R, a.rep) * (128 + 2) * 4;  // at most 33 KB
+        hipLaunchKernelGGL(k_kv_attn_gqa<NW>, grid, dim3(64 * NW), lds, s, a);
+    } else {
+        hipLaunchKernelGGL(k_kv_attn_mfma<NW>, grid, dim3(64 * NW), 0, s, a);
+    }
+    return hipGetLastError();
 }
 
-template <int NW>
 hipError_t go_attn_mfma(KvAttnArgs a, hipStream_t s)
 {
-    const int per = (a.rep + GQA_R - 1) / GQA_R, R = std::min(GQA_R, a.rep);
-    const int64_t blocks = a.rep == 1 ? a.nq : a.nq / a.rep * per;
-    a.splits = mfma_splits(a, blocks);
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        cus = 256;
+    const attn::Plan p = attn::plan(a.nq / a.rep, a.rep, a.seq_len, a.splits, cus);
+    a.splits = p.splits;
     a.chunk = (int)((((int64_t)a.seq_len + a.splits - 1) / a.splits + 63) / 64 * 64);
-    const dim3 grid((unsigned)blocks, (unsigned)a.splits);
-    if (a.rep == 1) {
-        hipLaunchKernelGGL(k_kv_attn_mfma<NW>, grid, dim3(64 * NW), 0, s, a);
-    } else {
-        const int lds = NW * R * (128 + 2) * 4;  // at most 33 KB
-        hipLaunchKernelGGL(k_kv_attn_gqa<NW>, grid, dim3(64 * NW), lds, s, a);
-    }
-    hipError_t e = hipGetLastError();
+    hipError_t e = p.waves == 8 ? go_attn_rows<8>(a, p.shared, s) : go_attn_rows<4>(a, p.shared, s);
     if (e != hipSuccess || a.splits == 1)
         return e;
     hipLaunchKernelGGL(k_kv_attn_combine<128>, dim3((unsigned)a.nq), dim3(128), 0, s, a);
@@ -804,8 +803,7 @@ hipError_t launch_kv_attention(const KvAttnArgs &a, hipStream_t s)
     case 64: return go_attn<64>(a, s);
     case 128:
         if (a.G == 128)
-            // a launch holds fewer than 2^32 threads
-            return a.nq < (1 << 23) ? go_attn_mfma<8>(a, s) : go_attn_mfma<4>(a, s);
+            return go_attn_mfma(a, s);
         return go_attn<128>(a, s);
     case 256: return go_attn<256>(a, s);
     }

@@ -42,7 +42,8 @@ def run(dev, orc, nkv, rep, s_max, seq, k=None, v=None, q=None):
     assert np.all(err <= 2.0 ** -10 * np.abs(ref) + 2.0 ** -16 * 9.0), err.max()
 
 
-# one query to five blocks of 8 per cache row
+# one query to 33 per cache row; few rows, so a block per query row takes them
+# (tests/native/attn_plan_check.cpp)
 @pytest.mark.parametrize("rep", [1, 2, 3, 5, 7, 8, 9, 16, 17, 33])
 # a token, part of a wave's 32, its edges, a block's 256 and its edges
 @pytest.mark.parametrize("seq", [1, 17, 32, 33, 255, 257])
@@ -56,6 +57,72 @@ def test_queries_per_cache_row(dev, orc, rep, seq):
     (129, 1, 1500), (256, 1, 513), (2, 4, 606), (2, 8, 1025), (5, 20, 2049), (40, 8, 4099)])
 def test_splits_of_a_row(dev, orc, nkv, rep, seq):
     run(dev, orc, nkv, rep, seq + seq % 3, seq)
+
+
+# blocks of 8 query rows (csrc/kv_attention.hip, k_kv_attn_gqa): one block to
+# five per cache row, whole and short ones, four and eight waves, a token, a
+# wave's 32, a block's 128 and 256 and their edges, whole rows and split ones.
+# The host check of the plan holds these calls to that kernel.
+SHARED = [(130, 2, 129), (130, 2, 257), (130, 2, 2049), (130, 3, 255), (130, 5, 65),
+          (130, 7, 257), (130, 8, 17), (130, 8, 33), (130, 9, 129), (130, 9, 255),
+          (130, 16, 33), (130, 17, 2049), (130, 33, 1), (130, 33, 257), (520, 2, 33),
+          (520, 2, 513), (520, 3, 17), (520, 5, 1), (520, 7, 1025), (60, 8, 513),
+          (60, 8, 1025), (60, 5, 2049), (300, 2, 1025), (300, 3, 2049)]
+
+
+@pytest.mark.parametrize("nkv,rep,seq", SHARED)
+def test_shared_cache_rows(dev, orc, nkv, rep, seq):
+    run(dev, orc, nkv, rep, seq + 5, seq)
+
+
+def test_shared_rows_growing_scores(dev, orc):
+    rng = np.random.default_rng(9)
+    k, v = rand_cache(rng, 60, 1500, 128, 128), rand_cache(rng, 60, 1500, 128, 128)
+    k[2][:] = np.linspace(-3, 3, 1500).astype(np.float16)[None, :, None]
+    q = (0.25 + 0.5 * np.abs(rng.standard_normal((480, 128)))).astype(np.float16)
+    run(dev, orc, 60, 8, 1500, 1500, k, v, q)
+
+
+def test_shared_rows_infinite_scores_and_scales(dev, orc):
+    """Tokens whose zero point is -inf weigh nothing, also where they fill whole
+    steps of a wave; an infinite value scale gives its infinity."""
+    import paper_2404_00456_amd as qq
+    rng = np.random.default_rng(10)
+    n, seq, cut = 130, 600, 333
+    k, v = rand_cache(rng, n, seq, 128, 128), rand_cache(rng, n, seq, 128, 128)
+    q = np.abs(rng.standard_normal((8 * n, 128))).astype(np.float16)
+    k[2][:, :cut] = -np.inf
+    full = H(qq.quarot_kv_decode_attention(T(q, dev), tuple(T(x, dev) for x in k),
+                                           tuple(T(x, dev) for x in v), seq))
+    part = orc.kv_attention(q, tuple(np.ascontiguousarray(x[:, cut:]) for x in k),
+                            tuple(np.ascontiguousarray(x[:, cut:]) for x in v), seq - cut, group=128)
+    d = np.abs(full.astype(np.float64) - part.astype(np.float64))
+    assert np.all(d <= 2.0 ** -10 * np.abs(part.astype(np.float64)) + 2.0 ** -16 * 9.0)
+    for inf in (np.inf, -np.inf):
+        k, v = rand_cache(rng, n, 40, 128, 128), rand_cache(rng, n, 40, 128, 128)
+        v[0][:, 0], v[1][:, 0] = 0x31, inf
+        q = (rng.standard_normal((8 * n, 128)) * 0.1).astype(np.float16)
+        out = H(qq.quarot_kv_decode_attention(T(q, dev), tuple(T(x, dev) for x in k),
+                                              tuple(T(x, dev) for x in v), 40))
+        assert np.all(out == inf)
+
+
+@pytest.mark.parametrize("nkv,rep,seq", [(16, 1, 3000), (300, 1, 2000), (60, 8, 1500),
+                                         (130, 2, 2049), (8, 8, 1000)])
+def test_same_bits_again(dev, nkv, rep, seq):
+    """The same call gives the same bits, whatever its workspace held."""
+    import torch
+    import paper_2404_00456_amd as qq
+    rng = np.random.default_rng(nkv + seq)
+    k, v = rand_cache(rng, nkv, seq, 128, 128), rand_cache(rng, nkv, seq, 128, 128)
+    k, v = tuple(T(x, dev) for x in k), tuple(T(x, dev) for x in v)
+    q = T((rng.standard_normal((nkv * rep, 128)) * 0.5).astype(np.float16), dev)
+    first = qq.quarot_kv_decode_attention(q, k, v, seq)
+    need = int(qq.lib().quarot_kv_attention_workspace_size(nkv * rep, seq, 128))
+    for fill in (0xFF, 0x7F, 0x00):
+        ws = torch.full((max(need, 16),), fill, dtype=torch.uint8, device=dev)
+        again = qq.quarot_kv_decode_attention(q, k, v, seq, workspace=ws)
+        assert torch.equal(first.view(torch.int16), again.view(torch.int16)), fill
 
 
 @pytest.mark.parametrize("rep", [1, 8])
