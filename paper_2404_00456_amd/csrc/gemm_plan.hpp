@@ -11,7 +11,7 @@ namespace gemm {
 enum class GemmKernel {
     K64,      // int4 codes with K not a multiple of 128: one 256 x 256 tile per block
     Tile256,  // persistent, 256 x 256 block tiles
-    Tile128,  // persistent, 128 x 256 block tiles, one wave per SIMD
+    Tile128,  // e3m2 only: persistent, 128 x 256 block tiles, one wave per SIMD
     Ksplit,   // e3m2 only: 128 x 256 tiles, k-steps split between two wave groups
 };
 
@@ -44,7 +44,8 @@ inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int bits, int cus, in
     constexpr int64_t KSPLIT_COST = 70;
     const bool ksplit =
         bits == 6 && K % 256 == 0 && K >= 512 && M > 128 && r128 * KSPLIT_COST < r256 * 100;
-    const bool m128 = ksplit || (ksteps >= stages && M > 128 && r128 * 90 < r256 * 100);
+    const bool m128 =
+        ksplit || (bits == 6 && ksteps >= stages && M > 128 && r128 * 90 < r256 * 100);
     const int64_t tiles = m128 ? t128 : t256;
     // persistent: one block per CU, or fewer for small problems (the LDS
     // ring allows one resident block per CU); with fewer than `stages`

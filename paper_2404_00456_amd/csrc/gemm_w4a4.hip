@@ -1225,18 +1225,6 @@ __global__ __launch_bounds__(Tile<256>::THREADS, 1) void k_gemm_w4a4_e3m2(GemmAr
 
 // 128 x 256 block tiles (four waves): for grids with too few 256 x 256
 // tiles to keep every compute unit busy.
-__global__ __launch_bounds__(Tile<128>::THREADS, 1) void k_gemm_w4a4_m128(GemmArgs a)
-{
-    extern __shared__ __align__(16) uint8_t lds[];
-    gemm_main<4, 128>(a, lds);
-}
-
-__global__ __launch_bounds__(Tile<128>::THREADS, 1) void k_gemm_w8a8_m128(GemmArgs a)
-{
-    extern __shared__ __align__(16) uint8_t lds[];
-    gemm_main<8, 128>(a, lds);
-}
-
 __global__ __launch_bounds__(Tile<128>::THREADS, 1) void k_gemm_w4a4_e3m2_m128(GemmArgs a)
 {
     extern __shared__ __align__(16) uint8_t lds[];
@@ -1316,10 +1304,8 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s, int bits)
         lds_bytes = KSPLIT_LDS;
         threads = KSPLIT_THREADS;
     } else if (m128) {
-        fn = bits == 8 ? (const void *)k_gemm_w8a8_m128
-             : bits == 6 ? (const void *)k_gemm_w4a4_e3m2_m128
-                         : (const void *)k_gemm_w4a4_m128;
-        lds_bytes = bits == 6 ? Ring<6, 128>::LDS : Ring<4, 128>::LDS;
+        fn = (const void *)k_gemm_w4a4_e3m2_m128;
+        lds_bytes = Ring<6, 128>::LDS;
         threads = Tile<128>::THREADS;
     } else {
         fn = bits == 8 ? (const void *)k_gemm_w8a8

@@ -952,8 +952,8 @@ __device__ __forceinline__ uint2 load_bits4(const RotArgs &a, int64_t off)
     }
 }
 
-// One row per block of four waves; the row's A = n / M groups of M
-// elements (element i = g M + b).
+// Rows of fewer than 16 groups of M elements (A = n / M = 2, 4 or 8), one per
+// block of four waves (element i = g M + b).
 //
 // m-factor on the int8 matrix cores.  It is a contraction, U = T . H_M
 // with T [A, M] the groups: every fp16 input is an integer multiple of
@@ -966,17 +966,15 @@ __device__ __forceinline__ uint2 load_bits4(const RotArgs &a, int64_t off)
 // exactly in binary64 and u = RN32(that * 2^-24): the exact sum rounded
 // once, as the definition asks, in whatever order the hardware adds.
 //
-// A wave takes row tiles of 16 groups (groups past A are zero); the MFMA
-// output puts groups 4 (l/16) + r (register r) and column ct*16 + l%16 in
-// lane l, so Walsh-Hadamard bits 0-1 of the group index are butterflies
-// between registers and bits 2-3 between lanes l and l ^ 16, l ^ 32; u is
-// then staged in LDS as the row itself (element i = g M + b at i).  Bits
-// 4.. (across tiles) run in registers on the 2^(k-4) values of one column
-// of the groups a, a + 16, ..., which also gives the row's absmax; the
-// epilogue reads 8 consecutive elements with two 16-byte reads.  H_M's
-// operand tiles sit in LDS in front of the row.
+// One wave takes the row's groups as a tile of 16 (groups past A are zero);
+// the MFMA output puts groups 4 (l/16) + r (register r) and column
+// ct*16 + l%16 in lane l, so Walsh-Hadamard bits 0-1 of the group index are
+// butterflies between registers and bit 2 between lanes l and l ^ 16; u is
+// then staged in LDS as the row itself (element i = g M + b at i), from which
+// all waves take the absmax and, 8 consecutive elements with two 16-byte reads,
+// the output.  H_M's operand tiles sit in LDS in front of the row.
 template <int M, int EPI, int PRO = PRO_PLAIN>
-__global__ __launch_bounds__(256, 2) void k_rot_largem(RotArgs a)
+__global__ __launch_bounds__(256, M == 108 ? 3 : 2) void k_rot_largem(RotArgs a)
 {
     constexpr int W = 4;
     constexpr int CT = HmMfmaB<M>::CT, KB = HmMfmaB<M>::KB;
@@ -999,12 +997,10 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem(RotArgs a)
     }
     __syncthreads();
 
-    const int RT = A >= 16 ? A / 16 : 1;  // row tiles of 16 groups
-    const int kreg = k < 4 ? k : 4;       // group bits done in registers / lanes
-    for (int rt = wave; rt < RT; rt += W) {
+    if (wave == 0) {
         // A operands: digit d of the 16 inputs b = kb*64 + (lane/16)*16 + e
-        // of group rt*16 + lane%16, byte e (zeros past the row or the group)
-        const int g = rt * 16 + (lane & 15);
+        // of group lane%16, byte e (zeros past the row or the group)
+        const int g = lane & 15;
         v4i dig[KB][7];
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
@@ -1066,38 +1062,34 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem(RotArgs a)
                     x = __builtin_fma(x, 4096.0, (double)acc[c][0][r]);
                     u[r] = (float)(x * 0x1p-24);  // exact scaling, one rounding
                 }
-                // Walsh-Hadamard bits 0..kreg-1 of the group index, bit 0
-                // first: registers (bits 0, 1), then lanes (bits 2, 3)
-                if (kreg > 0) {
+                // Walsh-Hadamard bits of the group index, bit 0 first: registers
+                // (bits 0, 1), then lanes (bit 2)
+                {
                     const float p0 = u[0], p2 = u[2];
                     u[0] = p0 + u[1];
                     u[1] = p0 - u[1];
                     u[2] = p2 + u[3];
                     u[3] = p2 - u[3];
                 }
-                if (kreg > 1) {
+                if (k > 1) {
                     const float p0 = u[0], p1 = u[1];
                     u[0] = p0 + u[2];
                     u[1] = p1 + u[3];
                     u[2] = p0 - u[2];
                     u[3] = p1 - u[3];
                 }
+                if (k > 2) {
+                    const bool hi = (lane & 16) != 0;
 #pragma unroll
-                for (int j = 2; j < 4; ++j) {
-                    if (kreg > j) {
-                        const int mask = 16 << (j - 2);
-                        const bool hi = (lane & mask) != 0;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float o = __shfl_xor(u[r], mask);
-                            u[r] = hi ? o - u[r] : u[r] + o;
-                        }
+                    for (int r = 0; r < 4; ++r) {
+                        const float o = __shfl_xor(u[r], 16);
+                        u[r] = hi ? o - u[r] : u[r] + o;
                     }
                 }
                 const int col = (c0 + c) * 16 + (lane & 15);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int gg = rt * 16 + 4 * (lane >> 4) + r;
+                    const int gg = 4 * (lane >> 4) + r;
                     if (gg < A && col < M)
                         rowbuf[gg * M + col] = u[r];
                 }
@@ -1105,43 +1097,10 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem(RotArgs a)
         }
     }
     __syncthreads();
-    // group bits 4.. (across row tiles) and the row's absmax: a thread takes
-    // column b of the groups a, a + 16, ... (a < 16), their 2^(k-4) values
     const float c = a.c;
     float amax = 0.0f;
-    auto column_pass = [&](auto NJ_) {
-        constexpr int NJ = decltype(NJ_)::value;
-        const int NA = NJ > 1 ? 16 : A;
-        for (int idx = tid; idx < NA * M; idx += 64 * W) {
-            const int al = idx / M, b = idx - al * M;
-            float v[NJ];
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                v[j] = rowbuf[(al + 16 * j) * M + b];
-#pragma unroll
-            for (int h = 1; h < NJ; h <<= 1)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    if (!(j & h)) {
-                        const float p = v[j], q = v[j + h];
-                        v[j] = p + q;
-                        v[j + h] = p - q;
-                    }
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if constexpr (NJ > 1)
-                    rowbuf[(al + 16 * j) * M + b] = v[j];
-                amax = fmaxf(amax, fabsf(v[j] * c));  // |y|: the sign of a zero is moot
-            }
-        }
-    };
-    switch (k) {
-    case 7: column_pass(std::integral_constant<int, 8>()); break;
-    case 6: column_pass(std::integral_constant<int, 4>()); break;
-    case 5: column_pass(std::integral_constant<int, 2>()); break;
-    default: column_pass(std::integral_constant<int, 1>()); break;
-    }
-    __syncthreads();
+    for (int i = tid; i < n; i += 64 * W)
+        amax = fmaxf(amax, fabsf(rowbuf[i] * c));  // |y|: the sign of a zero is moot
     const int chunks = n / 8;
     auto row8 = [&](int ch, float *y) {
         const float4 p0 = *reinterpret_cast<const float4 *>(rowbuf + ch * 8);
@@ -1159,8 +1118,7 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem(RotArgs a)
             store_y8<EPI>(a.out, row * n + ch * 8, y);
         }
     } else {
-        static_assert(EPI == EPI_SYM || EPI == EPI_SYM8 || EPI == EPI_E3M2,
-                      "large-m kernels serve activations");
+        static_assert(EPI == EPI_SYM || EPI == EPI_SYM8, "short rows have no e3m2 layout");
         static_for<6>([&](auto J) { amax = lane_max<J>(amax); });
         if (lane == 0)
             red[tid >> 6] = amax;
@@ -1173,45 +1131,14 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem(RotArgs a)
         const float s32 = (amax * a.clip) / qd;
         const uint16_t s16 = f2h(s32);
         const Divisor dv = make_divisor(h2f(s16));
-        if constexpr (EPI == EPI_E3M2) {
-            // a thread takes whole units (32 consecutive codes) through one
-            // fp6 pack conversion (code 2i from slot i of the first source,
-            // 2i + 1 from slot i of the second)
-            uint8_t *q6 = static_cast<uint8_t *>(a.out);
-            for (int u = tid; u < chunks / 4; u += 64 * W) {
-                v16f ev, od;
+        uint8_t *qr = static_cast<uint8_t *>(a.out) + row * sym_row_bytes<EPI>(n);
+        for (int ch = tid; ch < chunks; ch += 64 * W) {
+            float y[8];
+            row8(ch, y);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    float y[8];
-                    row8(4 * u + k, y);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float t = fminf(fmaxf(quotient(y[e] * c, dv), -8.0f), 7.0f);
-                        const float r = (t + 0x1.8p23f) - 0x1.8p23f;
-                        if (e & 1)
-                            od[4 * k + (e >> 1)] = r;
-                        else
-                            ev[4 * k + (e >> 1)] = r;
-                    }
-                }
-                v6i o = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(ev, od, 1.0f);
-                if (!dv.ok)  // zero or infinite scale: codes 0
-                    o = v6i{0, 0, 0, 0, 0, 0};
-                *reinterpret_cast<uint4 *>(q6 + e3m2_head(a.rows, row, u >> 2, u & 3)) =
-                    make_uint4((uint32_t)o[0], (uint32_t)o[1], (uint32_t)o[2], (uint32_t)o[3]);
-                *reinterpret_cast<uint2 *>(q6 + e3m2_tail(a.rows, row, u >> 2, u & 3)) =
-                    make_uint2((uint32_t)o[4], (uint32_t)o[5]);
-            }
-        } else {
-            uint8_t *qr = static_cast<uint8_t *>(a.out) + row * sym_row_bytes<EPI>(n);
-            for (int ch = tid; ch < chunks; ch += 64 * W) {
-                float y[8];
-                row8(ch, y);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    y[e] = y[e] * c;
-                store_codes8<EPI>(qr, ch * 8, y, dv, qd);
-            }
+            for (int e = 0; e < 8; ++e)
+                y[e] = y[e] * c;
+            store_codes8<EPI>(qr, ch * 8, y, dv, qd);
         }
         if (tid == 0)
             a.scale[row] = s16;
@@ -1928,17 +1855,26 @@ hipError_t go_largem(const RotArgs &a, hipStream_t s)
     case 128:
         if constexpr (M == 108)
             return go_largem_f16<M, 8, EPI, PRO>(a, s);
-        return hipErrorInvalidValue;
+        break;
+    case 2:
+    case 4:
+    case 8:
+        if constexpr (EPI != EPI_E3M2) {
+            // H_M's operand tiles, then the staged row
+            const size_t lds = (size_t)HmMfmaB<M>::CT * HmMfmaB<M>::KB * 1024 +
+                               (size_t)a.n * sizeof(float);
+            const void *fn = (const void *)k_rot_largem<M, EPI, PRO>;
+            hipError_t e =
+                hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess)
+                return e;
+            hipLaunchKernelGGL((k_rot_largem<M, EPI, PRO>), dim3((unsigned)a.rows), dim3(256), lds,
+                               s, a);
+            return hipGetLastError();
+        }
+        break;
     }
-    // H_M's operand tiles, then the staged row
-    const size_t lds = (size_t)HmMfmaB<M>::CT * HmMfmaB<M>::KB * 1024 +
-                       (size_t)a.n * sizeof(float);
-    const void *fn = (const void *)k_rot_largem<M, EPI, PRO>;
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL((k_rot_largem<M, EPI, PRO>), dim3((unsigned)a.rows), dim3(256), lds, s, a);
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 template <int EPI, bool ROT, int PRO, bool HEADS = false, bool KVROW = false>

@@ -35,12 +35,12 @@ int main()
         {16384, 28672, 8192, 4, 256, GemmKernel::Tile256, 256},
         {16384, 28672, 8192, 8, 256, GemmKernel::Tile256, 256},
         // Llama-2 7B at 2048 tokens: up keeps 344 large tiles in two rounds;
-        // down (128 large tiles) takes 256 128-row tiles, split k on e3m2
+        // down (128 large tiles) takes 256 128-row tiles on e3m2, with split k
         {2048, 11008, 4096, 6, 256, GemmKernel::Tile256, 256},
         {2048, 11008, 4096, 4, 256, GemmKernel::Tile256, 256},
         {2048, 4096, 11008, 6, 256, GemmKernel::Ksplit, 256},
-        {2048, 4096, 11008, 4, 256, GemmKernel::Tile128, 256},
-        {2048, 4096, 11008, 8, 256, GemmKernel::Tile128, 256},
+        {2048, 4096, 11008, 4, 256, GemmKernel::Tile256, 128},
+        {2048, 4096, 11008, 8, 256, GemmKernel::Tile256, 128},
         // int4 codes with K not a multiple of 128: one tile per block
         {300, 520, 100, 4, 256, GemmKernel::K64, 6},
         // split k needs M > 128, K a multiple of 256 and at least 512
