@@ -123,6 +123,59 @@ int main()
             ++failures;
         }
     }
+    // the shapes by which tests/test_gpu_gemm_tiled.py reaches the tiled kernels
+    typedef quarot::gemm::GemmKernel Kn;
+    const Kn L = Kn::Tile256, W = Kn::Tile128, X = Kn::Ksplit;
+    const struct {
+        long long M, N, K;
+        Kn kernel;
+    } tiled[] = {
+        {646, 33753, 128, L},   {646, 33753, 256, L},  {646, 33753, 384, L},   {646, 33753, 512, L},
+        {646, 33753, 640, L},   {650, 33764, 256, L},  {650, 33764, 768, L},   {388, 25203, 640, L},
+        {646, 33753, 64, L},    {646, 33753, 192, L},  {646, 33753, 320, L},   {650, 33764, 192, L},
+        {388, 25203, 320, L},   {260, 33753, 2176, W}, {270, 33764, 2176, W},
+        {519, 49162, 768, X},   {800, 33753, 1536, X}, {8317, 607, 8192, X},   {1409, 4100, 11008, X},
+        {1282, 11008, 4096, X}, {2047, 4095, 11008, X},
+    };
+    for (const auto &c : tiled)
+        for (int bits : {4, 6, 8}) {
+            // int8 codes: K to 320; int4 and e3m2 codes: K in 128s
+            if (bits == 8 ? c.K > 320 : c.K % 128 || (bits == 4 && c.kernel != L))
+                continue;
+            const auto p = plan_path(c.M, c.N, c.K, bits, 256, 3);
+            const auto g = quarot::gemm::plan_gemm(c.M, c.N, c.K, bits, 256, 3);
+            if (p.path != T || g.kernel != c.kernel) {
+                std::printf("FAIL M=%lld N=%lld K=%lld bits=%d: path %d kernel %d, want tiled %d\n", c.M,
+                            c.N, c.K, bits, (int)p.path, (int)g.kernel, (int)c.kernel);
+                ++failures;
+            }
+        }
+    // and test_gpu_gemm_stream.py and test_gpu_gemm_mid.py theirs, on every width
+    const struct {
+        long long M, N, K;
+        GemmPath path;
+        int a, b;
+    } reached[] = {
+        {1, 1, 128, S, 1, 1},       {5, 8190, 512, S, 1, 2},    {9, 8913, 256, S, 1, 4},
+        {14, 8915, 1152, S, 1, 4},  {17, 33, 512, S, 2, 1},     {17, 4442, 256, S, 2, 2},
+        {30, 4445, 1152, S, 2, 2},  {31, 8200, 512, S, 2, 4},   {17, 8913, 256, S, 2, 4},
+        {33, 64, 1024, S, 4, 1},    {40, 8190, 384, S, 4, 2},   {65, 2199, 256, S, 4, 2},
+        {100, 2201, 1152, S, 4, 2}, {65, 4442, 256, S, 4, 4},   {120, 4444, 640, S, 4, 4},
+        {75, 8190, 28672, D, 2, 1}, {70, 9003, 2048, D, 2, 2},  {250, 9002, 1152, D, 4, 2},
+        {500, 9001, 1152, D, 4, 3}, {700, 9004, 640, D, 4, 4},  {1000, 9001, 512, D, 8, 3},
+        {1500, 16001, 128, D, 8, 3}, {61, 16390, 256, D, 2, 2}, {500, 9001, 320, D, 4, 3},
+    };
+    for (const auto &c : reached)
+        for (int bits : {4, 6, 8}) {
+            if (bits != 8 && c.K % 128)
+                continue;
+            const auto p = plan_path(c.M, c.N, c.K, bits, 256, 3);
+            if (p.path != c.path || p.a != c.a || p.b != c.b) {
+                std::printf("FAIL M=%lld N=%lld K=%lld bits=%d: path %d tile %d x %d, want %d %d x %d\n",
+                            c.M, c.N, c.K, bits, (int)p.path, p.a, p.b, (int)c.path, c.a, c.b);
+                ++failures;
+            }
+        }
     if (failures)
         return 1;
     std::printf("ok\n");

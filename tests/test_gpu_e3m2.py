@@ -97,19 +97,19 @@ def _gemm_case(dev, orc, M, N, K, xq, wq, sx, sw):
                                    (256, 256, 28672), (2, 3, 65536),
                                    (2048, 8448, 128), (2048, 8448, 256), (2048, 8448, 384),
                                    (2304, 8448, 512), (2200, 8400, 1024),
-                                   # whole 256 x 256 tiles and an even number of
-                                   # k-steps (four 128 x 128 waves per block):
-                                   # one tile, one per block, several per block
+                                   # whole 256 x 256 tiles, an even number of
+                                   # k-steps (the tiled kernel takes 2048 x 8192,
+                                   # 4096 x 8192 and 8192 x 4096)
                                    (512, 512, 1024), (2048, 8192, 1280), (4096, 8192, 512),
                                    (8192, 4096, 768), (4352, 4352, 1536),
-                                   # 128-row tiles with split k-steps: the
-                                   # fewest pairs (K = 512), one row past a
-                                   # tile, N not a multiple of 4, one column
-                                   # of tiles
+                                   # one row past a 128-row tile, N not a
+                                   # multiple of 4, one column of tiles (the
+                                   # streaming kernels)
                                    (129, 300, 512), (1000, 36, 768), (640, 1030, 2048)])
 def test_gemm_e3m2_exact(dev, orc, M, N, K):
     """Ragged edges, k-step counts below, at and above the LDS ring depth,
-    blocks that walk several tiles, the largest K."""
+    the largest K: mostly the streaming and middling kernels
+    (test_gpu_gemm_tiled.py has the tiled ones)."""
     say(f"e3m2 gemm M={M} N={N} K={K}")
     rng = np.random.default_rng(M * 7 + N * 3 + K + 1)
     xq = rand_codes(rng, M, K)
@@ -173,14 +173,12 @@ def test_gemm_e3m2_full_size(dev, orc, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(2048, 11008, 4096), (2048, 4096, 11008),
-                                   # 128-row tiles with split k-steps, one or
-                                   # two tiles per block, a ragged last column
-                                   # of tiles
+                                   # a ragged last column of tiles
                                    (384, 33000, 512)])
 def test_gemm_e3m2_7b_shapes(dev, orc, M, N, K):
     """Llama-2-7B FFN shapes at 2048 tokens, in the launch configuration the
-    benchmark times, and a grid whose blocks walk two 128-row tiles with
-    split k-steps: every acc and y equal to the int4 path's, and one seeded
+    benchmark times (middling tiles up, split k-steps down), and middling
+    tiles in more blocks than CUs: every acc and y equal to the int4 path's, and one seeded
     row of every 128-row tile, plus the first and last, equal to the
     oracle's, with and without the int32 output."""
     import torch
@@ -213,8 +211,7 @@ def test_gemm_e3m2_7b_shapes(dev, orc, M, N, K):
 @pytest.mark.parametrize("case", range(24))
 def test_gemm_e3m2_random_grids(dev, orc, case):
     """Seeded random shapes with more than 128 rows and K a multiple of 256
-    (the tile walks of both e3m2 kernels, one to three tiles per block,
-    ragged edges): every acc and y equal to the int4 path's, with and
+    (streaming, middling and 256-row kernels, ragged edges): every acc and y equal to the int4 path's, with and
     without the int32 output, and two seeded rows equal to the oracle's."""
     import torch
     import paper_2404_00456_amd as q

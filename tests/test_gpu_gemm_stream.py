@@ -28,9 +28,13 @@ def dev():
     (63, 100, 1152), (64, 65, 4096), (65, 48, 4224), (130, 31, 4352),
     # more than one run of k-steps per wave, an odd and an even number
     (3, 40, 8192), (20, 40, 12416), (50, 24, 28672), (2, 3, 65536),
-    # 32 and 64 columns per block (a block per CU at 256 CUs), ragged last
-    (5, 8190, 512), (31, 8200, 512), (40, 8190, 384), (9, 20001, 256), (29, 16390, 256),
-    (61, 16390, 256), (200, 4100, 512)])
+    # 32 and 64 columns per block (a block per CU at 256 CUs), ragged last, on
+    # 16, 32 and 64 rows
+    (5, 8190, 512), (31, 8200, 512), (40, 8190, 384), (9, 8913, 256), (14, 8915, 1152),
+    (17, 4442, 256), (30, 4445, 1152), (17, 8913, 256), (65, 2199, 256), (100, 2201, 1152),
+    (65, 4442, 256), (120, 4444, 640),
+    # more blocks than CUs and few k-steps: the middling kernels
+    (9, 20001, 256), (29, 16390, 256), (61, 16390, 256), (200, 4100, 512)])
 def test_gemm_stream_exact(dev, orc, fmt, M, N, K):
     import paper_2404_00456_amd as q
     say(f"stream gemm {fmt} M={M} N={N} K={K}")

@@ -54,8 +54,8 @@ def rand_group_case(seed, M, N, K, group):
     (1, 1, 128, 128), (16, 256, 128, 64), (255, 257, 256, 128), (300, 520, 1024, 256),
     (513, 100, 4096, 128), (64, 1000, 11008, 64), (64, 1000, 11008, 128),
     (40, 300, 11008, 256), (2, 3, 65536, 64), (7, 129, 65536, 256),
-    # M, N multiples of 8 (the persistent ring kernel): ragged tiles, fewer
-    # k-steps than ring stages (one tile per block), a single k-step
+    # M, N multiples of 8: the persistent ring kernel from 513 rows on (the
+    # few-row kernel takes most smaller ones)
     (8, 8, 256, 256), (264, 136, 2048, 128), (1024, 1024, 256, 128), (520, 392, 128, 64),
     (24, 8192, 65536, 128), (16, 264, 65536, 256), (8, 136, 65536, 64)])
 def test_gemm_grouped(dev, orc, M, N, K, group):
@@ -81,6 +81,46 @@ def test_gemm_grouped_few_rows(dev, orc, M, N, groups, group):
     ry = orc.gemm_grouped(xq, sx, wq, sw, group=group)
     assert_same(H(y).view(np.uint16), ry.view(np.uint16),
                 f"grouped few rows M={M} N={N} K={K} G={group}")
+
+
+# More than 512 rows, which the few-row kernel does not take: the tiles without
+# a ring (M or N no multiple of 8) and the ring, ragged in both directions, one
+# k-step, one group, several and many
+@pytest.mark.parametrize("group", [64, 128, 256])
+@pytest.mark.parametrize("M,N,K", [(517, 131, 256), (517, 130, 512), (515, 36, 16384), (519, 260, 1792),
+                                   (520, 136, 256), (520, 392, 512), (520, 136, 32768), (776, 264, 1792)])
+def test_gemm_grouped_more_rows(dev, orc, M, N, K, group):
+    import paper_2404_00456_amd as q
+    say(f"grouped gemm M={M} N={N} K={K} group={group}")
+    xq, sx, wq, sw = rand_group_case(M * 11 + N + K + group, M, N, K, group)
+    y = q.quarot_w4a4_gemm_grouped(T(xq, dev), T(sx, dev), T(wq, dev), T(sw, dev), group=group)
+    ry = orc.gemm_grouped(xq, sx, wq, sw, group=group)
+    assert_same(H(y).view(np.uint16), ry.view(np.uint16), f"grouped M={M} N={N} K={K} G={group}")
+
+
+# one k-step of 128: a group of 128 or two of 64
+@pytest.mark.parametrize("M,N,group", [(517, 131, 64), (517, 131, 128), (520, 136, 64), (520, 136, 128)])
+def test_gemm_grouped_one_step(dev, orc, M, N, group):
+    test_gemm_grouped_more_rows(dev, orc, M, N, 128, group)
+
+
+@pytest.mark.parametrize("group", [64, 128, 256])
+@pytest.mark.parametrize("M,N", [(517, 259), (520, 264), (60, 259)])
+def test_gemm_grouped_extreme_codes(dev, orc, M, N, group):
+    """All -8 codes and scales down to fp16 subnormals on the tiles without a
+    ring, the ring and the few-row kernel."""
+    import paper_2404_00456_amd as q
+    K = 2048
+    rng = np.random.default_rng(M + N + group)
+    xq = np.full((M, K // 2), 0x88, np.uint8)
+    wq = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    wq[0] = 0x88
+    sx = (2.0 ** rng.uniform(-24, -14, (K // group, M))).astype(np.float16)
+    sw = (2.0 ** rng.uniform(-14, -8, (K // group, N))).astype(np.float16)
+    y = q.quarot_w4a4_gemm_grouped(T(xq, dev), T(sx, dev), T(wq, dev), T(sw, dev), group=group)
+    ry = orc.gemm_grouped(xq, sx, wq, sw, group=group)
+    assert (np.abs(ry.astype(np.float32)) < 2.0 ** -14).mean() > 0.05
+    assert_same(H(y).view(np.uint16), ry.view(np.uint16), f"grouped extremes M={M} N={N} G={group}")
 
 
 @pytest.mark.parametrize("M,N,K,group", [(2200, 8400, 1024, 128), (2048, 8448, 512, 64),

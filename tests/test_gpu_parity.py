@@ -199,10 +199,10 @@ def test_gemm_exact(dev, orc, M, N, K):
 @pytest.mark.parametrize("M,N,K", [(2048, 8448, 128), (2048, 8448, 256), (2048, 8448, 384),
                                    (2048, 8448, 640), (2304, 8448, 512), (2200, 8400, 1024)])
 def test_gemm_many_tiles(dev, orc, M, N, K):
-    """More 256 x 256 tiles than one wave of blocks (264 and 297 tiles), so
-    that blocks walk several tiles: k-step counts below, at and above the
-    LDS ring depth, tile counts with and without a multiple of 8, ragged
-    edges."""
+    """More tiles than one wave of blocks on the middling kernels: k-step
+    counts below, at and above the LDS ring depth, tile counts with and
+    without a multiple of 8, ragged edges (test_gpu_gemm_tiled.py has the
+    256 x 256 tiles)."""
     import paper_2404_00456_amd as q
     say(f"gemm many tiles M={M} N={N} K={K}")
     rng = np.random.default_rng(M + N + K)
