@@ -2,9 +2,13 @@
 hazards that hand-written assembly in the kernels could create and the
 compiler cannot see through: a DPP instruction reading a VGPR within two
 wait states of the VALU instruction that wrote it (the DPP butterflies and
-lane max/min blocks are inline asm), and an LDS-DMA load
+lane max/min blocks are inline asm), an LDS-DMA load
 (global_load_lds_*) within one wait state of an SALU write of M0 (the
-GEMMs' DMA blocks set M0 themselves).
+GEMMs' DMA blocks set M0 themselves), and a DPP or lane-permute
+instruction reading or writing a VGPR within 19 wait states of a matrix
+instruction that writes it (what the longest of them needs; an output
+register that is not read any more may be given to the asm while the
+matrix instruction still writes it).
 
 The code objects are taken from the built libquarot.so (its .hip_fatbin
 section, one offload bundle per source file) and disassembled with the
@@ -84,14 +88,15 @@ def check(text):
     bad = []
     func = "?"
     recent = []  # (wait states since, mnemonic, vgprs written, writes m0)
+    mfma = []  # (wait states since, mnemonic, vgprs written)
     for raw in text.splitlines():
         s = raw.strip()
         m = re.match(r"^[0-9a-f]+ <(.+)>:$", s)
         if m:
-            func, recent = m.group(1), []
+            func, recent, mfma = m.group(1), [], []
             continue
         if s.endswith(":") or s.startswith("<"):
-            recent = []  # a label: another path may enter here
+            recent, mfma = [], []  # a label: another path may enter here
             continue
         p = parse(raw)
         if p is None or p[0].startswith((".", "Disassembly")):
@@ -106,6 +111,11 @@ def check(text):
                 if waits < 2 and pmn.startswith("v_") and src0 & pregs:
                     bad.append((func, s, f"DPP reads v{sorted(src0 & pregs)} {waits} wait "
                                          f"state(s) after {pmn} wrote it"))
+        if is_dpp or mn.startswith("v_permlane"):
+            for waits, pmn, pregs in mfma:
+                if vregs(ops) & pregs:
+                    bad.append((func, s, f"v{sorted(vregs(ops) & pregs)} {waits} wait state(s) after "
+                                         f"{pmn} began to write it"))
         if "_lds_" in mn and mn.startswith(("global_load", "buffer_load")):
             for waits, pmn, _, wm0 in recent:
                 if wm0 and waits < 1:
@@ -113,6 +123,13 @@ def check(text):
         # age the window: s_nop N gives N + 1 wait states, anything else one
         step = int(ops, 0) + 1 if mn == "s_nop" else 1
         recent = [(w + step, a, b, c) for (w, a, b, c) in recent if w + step < 8]
+        mfma = [(w + step, a, b) for (w, a, b) in mfma if w + step < 19]
+        if mn != "s_nop" and not is_dpp and not mn.startswith("v_permlane"):
+            # written since by an instruction that the compiler placed, waits included
+            dst = vregs(ops.split(",")[0]) if mn.startswith("v_") else set()
+            mfma = [(w, a, b - dst) for (w, a, b) in mfma]
+        if mn.startswith("v_mfma"):
+            mfma.append((0, mn, vregs(ops.split(",")[0])))
         if mn != "s_nop":
             fields = [f.strip() for f in ops.split(",")]
             dst = fields[0] if fields else ""
@@ -128,7 +145,9 @@ def test_no_dpp_or_m0_hazards():
     assert len(texts) >= 5  # one code object per source file with kernels
     ndpp = sum(t.count("_dpp") + t.count("quad_perm") for t in texts)
     nlds = sum(t.count("global_load_lds") for t in texts)
-    assert ndpp > 100 and nlds > 10  # the checked patterns are present
+    nswap = sum(t.count("v_permlane") for t in texts)
+    nmfma = sum(t.count("v_mfma") for t in texts)
+    assert ndpp > 100 and nlds > 10 and nswap > 100 and nmfma > 100  # the checked patterns are present
     bad = [v for t in texts for v in check(t)]
     assert not bad, "\n".join(f"{f}: {l}: {m}" for f, l, m in bad[:20])
 
@@ -149,3 +168,15 @@ def test_checker_sees_a_planted_hazard():
     assert check(good) == []
     found = check(bad)
     assert len(found) == 2 and "DPP" in found[0][2] and "m0" in found[1][2]
+    good = """0000000000000000 <k>:
+\tv_mfma_f32_16x16x32_f16 v[8:11], v[0:3], v[4:7], v[8:11]
+\ts_nop 15
+\ts_nop 2
+\tv_permlane32_swap_b32_e32 v10, v12
+"""
+    assert check(good) == []
+    assert len(check(good.replace("\ts_nop 2\n", "\ts_nop 1\n"))) == 1
+    assert check(good.replace("\ts_nop 15\n", "").replace("v10", "v13")) == []
+    dpp = "\tv_add_f32_dpp v8, v20, v21 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+    assert len(check(good.replace("\tv_permlane32_swap_b32_e32 v10, v12\n", "").replace(
+        "\ts_nop 15\n", "") + dpp)) == 1
