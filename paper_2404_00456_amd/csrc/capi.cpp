@@ -75,6 +75,9 @@ bool fake_hip_error(const char *call)
     return v && call && std::strcmp(v, call) == 0;
 }
 
+// The device this thread's last check accepted and its compute units.
+thread_local int ok_dev = -1, ok_cus = 256;
+
 // The device of the calling thread must be a gfx950.  Cached per thread
 // and device (a host-side query, no device work).  `call` names the entry
 // point (for the failure injection above).
@@ -88,7 +91,6 @@ quarot_status check_device(const char *call)
         g_last_hip_error = (int)e;
         return QUAROT_ERR_NO_DEVICE;
     }
-    thread_local int ok_dev = -1;
     if (ok_dev == dev)
         return QUAROT_OK;
     hipDeviceProp_t prop;
@@ -99,6 +101,7 @@ quarot_status check_device(const char *call)
     }
     if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
         return QUAROT_ERR_NO_DEVICE;
+    ok_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     ok_dev = dev;
     return QUAROT_OK;
 }
@@ -1135,6 +1138,7 @@ quarot_status quarot_kv_decode_attention(const quarot_f16 *q, const uint8_t *k_c
     a.G = (int)group;
     a.splits = kv_attn_splits(nq, seq_len);
     a.chunk = (int)(((seq_len + a.splits - 1) / a.splits + 63) / 64 * 64);
+    a.cus = ok_cus;
     a.sm_scale = sm_scale;
     hipError_t e = launch_kv_attention(a, (hipStream_t)stream);
     return e == hipSuccess ? QUAROT_OK : hip_fail(e);

@@ -208,6 +208,7 @@ struct KvAttnArgs {
     int seq_len;
     int D, G;
     int splits, chunk;  // sequence split: tokens [s * chunk, (s + 1) * chunk)
+    int cus;            // the device's compute units
     float sm_scale;
 };
 

@@ -271,8 +271,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void k_kv_attn(KvAttnArgs a)
 // Values: v_mfma_f32_16x16x16_f16 with A = the tokens' weights p_t vs_t and
 // B = the V codes, contracting over the 16 tokens.  Of the 16 rows of A, eight
 // hold the weights' fp16 values and eight the fp16 rests, so that the sum of
-// two output rows keeps 22 bits of each weight at no further matrix
-// instruction.  Lane l loads code bytes 4 n .. 4 n + 3 (elements 8 n .. 8 n +
+// two output rows keeps up to 22 bits of each weight (split_h) at no further
+// matrix instruction.  Lane l loads code bytes 4 n .. 4 n + 3 (elements 8 n .. 8 n +
 // 7) of tokens 4 g .. 4 g + 3, and output column n of step dc = 0..7
 // accumulates element 8 n + dc.  The zero-point term sum_t p_t vz_t and the
 // softmax sums stay in binary32.
@@ -319,8 +319,9 @@ __device__ __forceinline__ _Float16 bits_h(uint32_t b)
     return __builtin_bit_cast(_Float16, (uint16_t)b);
 }
 
-// w as fp16 in the low half and the fp16 rest in the high one (w's 22 leading
-// bits together; infinities stay what they are)
+// w as fp16 in the low half and the fp16 rest in the high one (infinities stay
+// what they are): w's 22 leading bits together while the rest is a normal fp16,
+// from about 2^-3 on; below, w to 2^-25
 __device__ __forceinline__ uint32_t split_h(float w)
 {
     const _Float16 hi = (_Float16)w;
@@ -778,12 +779,7 @@ hipError_t go_attn_rows(const KvAttnArgs &a, bool shared, hipStream_t s)
 
 hipError_t go_attn_mfma(KvAttnArgs a, hipStream_t s)
 {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-        cus = 256;
-    const attn::Plan p = attn::plan(a.nq / a.rep, a.rep, a.seq_len, a.splits, cus);
+    const attn::Plan p = attn::plan(a.nq / a.rep, a.rep, a.seq_len, a.splits, a.cus);
     a.splits = p.splits;
     a.chunk = (int)((((int64_t)a.seq_len + a.splits - 1) / a.splits + 63) / 64 * 64);
     hipError_t e = p.waves == 8 ? go_attn_rows<8>(a, p.shared, s) : go_attn_rows<4>(a, p.shared, s);
