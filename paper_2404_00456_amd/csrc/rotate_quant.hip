@@ -1190,7 +1190,9 @@ __device__ __forceinline__ void f16_split_wide(uint32_t bits, v2h &w, v2h &h, v2
     auto h2 = [](uint32_t u) { return __builtin_bit_cast(v2h, u); };
     const uint32_t e = (((bits & 0x7C007C00u) + 0x04000400u) >> 5) & 0x04000400u;
     const v2h x = h2(bits ^ e);
-    w = rint2(x * h2(0x1C001C00u + e));  // 2^-8, or 2^-7
+    // 2^-8, or 2^-7; to the nearest integer as the sum with 1.5 2^10 rounds
+    const v2h magic = h2(0x66006600u);
+    w = __builtin_elementwise_fma(x, h2(0x1C001C00u + e), magic) - magic;
     const v2h s = __builtin_elementwise_fma(w, h2(0xDC00DC00u - e), x) *  // -256, or -128
                   h2(0x58005800u + e);                                    // 128, or 256
     h = rint2(s);
@@ -1216,7 +1218,7 @@ struct LargemLds {
 // order, and fma(sum l, 2^-10, sum h) is 2^7 u with the one rounding the
 // definition asks for.  The factor 2^-7 joins c, exactly.  (A row with larger
 // values takes a third operand and binary64 at the end, see below: 2048 x 11008,
-// SwiGLU, all rows such: 100 us, 91 without the step of the exponent.)
+// SwiGLU, all rows such: 98 us, 91 without the step of the exponent.)
 //
 // The four waves split the row into operands, 32 inputs of 16 groups at a
 // time, through LDS; each then multiplies all groups by the column tiles
@@ -1230,9 +1232,10 @@ struct LargemLds {
 // of them on its 7-digit planes and the binary64 sums of 4 products per
 // output; the split takes 5 and the sum 1.  7B down projection input
 // (2048 x 11008, SwiGLU): 109 -> 71 us; 517 x 13824, int8 codes: 34 -> 20 us.
-// What is left is mostly the SiLU (about 30 instructions per element) and the
-// quantizer.  Six or eight waves per block were slower (108 us; 24 us): they
-// leave one block per CU.
+// The VALU is busy for half of the former's time and the matrix cores for 11%:
+// SiLU (about 30 instructions per element), split, products and codes of a row
+// follow each other between barriers.  Six or eight waves per block were slower
+// (108 us; 24 us): they leave one block per CU.
 template <int M, int RT, int EPI, int PRO>
 __global__ __launch_bounds__(256, 2) void k_rot_largem_f16(RotArgs a)
 {
