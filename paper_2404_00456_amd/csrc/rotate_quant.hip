@@ -1381,7 +1381,7 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem_f16(RotArgs a)
 #pragma unroll
                 for (int i = 0; i < CTW; ++i)
                     sw[i] = sh[i] = sl[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
+#pragma unroll
                 for (int kb = 0; kb < KB; ++kb) {
                     const uint4 tv = __builtin_bit_cast(uint4, plane(0, rt, kb));
                     const uint32_t tw[4] = {tv.x, tv.y, tv.z, tv.w};
@@ -1396,9 +1396,7 @@ __global__ __launch_bounds__(256, 2) void k_rot_largem_f16(RotArgs a)
                     }
 #pragma unroll
                     for (int i = 0; i < CTW; ++i) {
-                        // (from the table: H is indexed at compile time)
-                        const v8h Hk = __builtin_bit_cast(
-                            v8h, hsrc[(min(wave + W * i, CT - 1) * KB + kb) * 64]);
+                        const v8h Hk = H[i][kb];
                         sw[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, wv, sw[i], 0, 0, 0);
                         sh[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, hv, sh[i], 0, 0, 0);
                         sl[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Hk, lv, sl[i], 0, 0, 0);
