@@ -1218,7 +1218,7 @@ struct LargemLds {
 // order, and fma(sum l, 2^-10, sum h) is 2^7 u with the one rounding the
 // definition asks for.  The factor 2^-7 joins c, exactly.  (A row with larger
 // values takes a third operand and binary64 at the end, see below: 2048 x 11008,
-// SwiGLU, all rows such: 98 us, 91 without the step of the exponent.)
+// SwiGLU, back to back: 79 us where all rows are such, 53 where none is.)
 //
 // The four waves split the row into operands, 32 inputs of 16 groups at a
 // time, through LDS; each then multiplies all groups by the column tiles
@@ -1231,8 +1231,8 @@ struct LargemLds {
 // The digit kernel above spends about 94 VALU instructions per element, most
 // of them on its 7-digit planes and the binary64 sums of 4 products per
 // output; the split takes 5 and the sum 1.  7B down projection input
-// (2048 x 11008, SwiGLU): 109 -> 71 us; 517 x 13824, int8 codes: 34 -> 20 us.
-// The VALU is busy for half of the former's time and the matrix cores for 11%:
+// (2048 x 11008, SwiGLU): 109 -> 62 us; 517 x 13824, int8 codes: 34 -> 17 us.
+// The VALU is busy for half of the former's time and the matrix cores for 12%:
 // SiLU (about 30 instructions per element), split, products and codes of a row
 // follow each other between barriers.  Six or eight waves per block were slower
 // (108 us; 24 us): they leave one block per CU.
@@ -1841,7 +1841,13 @@ hipError_t go_largem_f16(const RotArgs &a, hipStream_t s)
     // 512 blocks (two per CU) take the rows in turn.  Fewer blocks of equally many
     // rows each put two on some CUs and one on others: 517 x 13824 int4 codes 19.1
     // us, this 15.5; 777 rows 19.6 and 20.1; 1025 26.4 and 21.8; 2048 37.0 both.
-    const int64_t grid = std::min<int64_t>(a.rows, 512);
+    // More than 1024 SwiGLU rows take 1024 blocks: for n = 6912 three fit a CU (162
+    // registers; 5000 rows 80 -> 73 us), and the others measure no worse (5000 x 5504
+    // 72 -> 69, 2048 x 13824 65.4 -> 63.6, x 11008 52.9 -> 51.8).  With fewer rows
+    // (517 x 13824 23.1 -> 24.8) or no SwiGLU (2048 x 11008 to fp16 30.1 -> 31.4)
+    // they would.
+    const int64_t most = PRO == PRO_SWIGLU && a.rows > 1024 ? 1024 : 512;
+    const int64_t grid = std::min(a.rows, most);
     hipLaunchKernelGGL((k_rot_largem_f16<M, RT, EPI, PRO>), dim3((unsigned)grid), dim3(256), lds, s,
                        a);
     return hipGetLastError();

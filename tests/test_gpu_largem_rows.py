@@ -88,6 +88,23 @@ def test_largem_swiglu_edge_rows(dev, orc, n):
     assert_same(H(s6).view(np.uint16), rs.view(np.uint16), f"swiglu e3m2 scales n={n}")
 
 
+@pytest.mark.parametrize("n,rows", [(1728, 1024), (1728, 1025), (2752, 2049)])
+def test_largem_swiglu_row_counts(dev, orc, n, rows):
+    """512 blocks up to 1024 rows, 1024 blocks past them: every row is written
+    once, also the wide ones of a block's second and third turn."""
+    import paper_2404_00456_amd as q
+    say(f"largem swiglu row counts n={n} rows={rows}")
+    rng = np.random.default_rng(rows)
+    gate = (rng.standard_normal((rows, n)) * 1.5).astype(np.float16)
+    up = rng.standard_normal((rows, n)).astype(np.float16)
+    up[::7] *= np.float16(300)
+    up[rows - 1, 0], gate[rows - 1, 0] = 60.0, 10.0
+    rq, rs = orc.swiglu_quant_int4(gate, up, rotate=True, clip=0.9)
+    codes, scale = q.quarot_swiglu_quant_int4(T(gate, dev), T(up, dev), clip_ratio=0.9)
+    assert_same(H(codes), rq, f"swiglu int4 codes n={n} rows={rows}")
+    assert_same(H(scale).view(np.uint16), rs.view(np.uint16), f"swiglu int4 scales n={n} rows={rows}")
+
+
 def test_swiglu_infinite_gate(dev):
     """silu(+inf) = inf and silu(-inf) = -inf / (1 + e^88) = -inf in the
     binary32 recipe; NaN stays NaN."""
