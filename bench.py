@@ -214,10 +214,12 @@ def event_times_us(torch, stream, fns, iters):
 def rotation_bounds(q, M, K, code_bits):
     """(HBM-bound us, VALU-bound us) of rotate+quantize: algorithmic bytes at
     8 TB/s, and log2(2^k) butterfly adds plus m - 1 m-factor adds per
-    element at the fp32 vector add rate."""
+    element at the fp32 vector add rate (m = 108 and 172 run their m-factor
+    on the matrix cores, so only the butterflies count there)."""
     k2, m = q.quarot_hadamard_factor(K)
+    adds = k2 + (m - 1 if m < 108 else 0)
     return (rotate_bytes(M, K, code_bits) / (PEAK_HBM_GBS * 1e9) * 1e6,
-            M * K * (k2 + m - 1) / PEAK_F32_ADDS * 1e6)
+            M * K * adds / PEAK_F32_ADDS * 1e6)
 
 
 def bench_layers_7b(q, workloads, torch, np, dev, stream, iters, keep=None):
