@@ -515,9 +515,10 @@ __global__ __launch_bounds__(64 * NW)
 // row reads and unpacks it rep times.  Past 8 rows a cache row takes several
 // blocks.  40 cache rows of 8 queries over 4099 tokens: 14.8 us with the
 // combining pass, 37 as 320 blocks of one query each; 192 x 8 over 3000
-// tokens (78 MB): 28.6 us.  What bounds the long ones is the
-// unpacking (two vector instructions per code pair, K and V), the short ones
-// the chain of one load, two matrix products and a reduction per 32 tokens.
+// tokens (78 MB): 31 us, VALU busy 44% (the unpacking, two vector instructions
+// per code pair, K and V) and MFMA 8%, on 192 of 256 CUs.  What bounds the
+// short ones is the chain of one load, two matrix products and a reduction per
+// 32 tokens.
 //
 // Scores: A = the K codes (16 tokens), B = the queries (columns n and n + 8
 // query n; past R the last one), so lane l gets query l % 8 against tokens

@@ -2,7 +2,8 @@
 row, where several query rows share a cache row and where a row's tokens are
 split over blocks, against the CPU oracle.
 
-The bound: the kernel keeps 22 bits of the weights times the value scales,
+The bound: the kernel keeps 22 bits of the weights times the value scales (of
+those below 2^-3 what is above 2^-25, errors that cancel over the tokens),
 accumulates in binary32 and rounds the result to fp16 (2^-11 of it), so with
 weights summing to 1 the error is at most 2^-11 |out| plus binary32 terms of
 the size of scale * code, at most 0.6 * 15 = 9 here: exp and the scores'
