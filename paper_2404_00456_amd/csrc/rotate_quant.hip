@@ -1218,7 +1218,7 @@ struct LargemLds {
 // order, and fma(sum l, 2^-10, sum h) is 2^7 u with the one rounding the
 // definition asks for.  The factor 2^-7 joins c, exactly.  (A row with larger
 // values takes a third operand and binary64 at the end, see below: 2048 x 11008,
-// SwiGLU, back to back: 79 us where all rows are such, 53 where none is.)
+// SwiGLU, back to back: 76 us where all rows are such, 51 where none is.)
 //
 // The four waves split the row into operands, 32 inputs of 16 groups at a
 // time, through LDS; each then multiplies all groups by the column tiles
